@@ -62,6 +62,23 @@ def test_ties_and_exact_boundaries(mb):
     _same(*_both(mb, d, np.array([0, 6], np.int32), e, dict(POL)))
 
 
+@pytest.mark.parametrize("count,copies,theta", [(1, 1, 60.0), (64, 1, 15.0), (126, 2, 89.5), (128, 1, 90.0), (129, 1, 0.0),
+                                               (128, 3, 89.0)])
+def test_ranking_and_cone_edges(mb, count, copies, theta):
+    """Frames up to and past the largest that is ranked by counting, equal and nearly equal ranking keys (repeated
+    detections, positions one unit in the last place apart), detections on the cone's edge to the last bits, and cones
+    on both sides of the steepest that is decided by the tangent."""
+    d, off, e = synth.detections(70 + count, 3, count=[count, 0, count])
+    n = len(d)
+    d[:n - n // copies] = d[n // copies:][:n - n // copies] if copies > 1 else d[:0]
+    d["x"][::5] = np.nextafter(d["x"][::5], np.inf)
+    d["vx"][1::4] = d["vy"][1::4] = 0.0
+    e["dyaw"], e["dx"], e["dy"] = 0.0, 0.0, 0.0
+    d["x"][1::4] = np.abs(d["x"][1::4])
+    d["y"][1::4] = d["x"][1::4] * np.tan(np.radians(theta)) * (1.0 + np.arange(len(d[1::4])) % 5 * 2.0 ** -52)
+    _same(*_both(mb, d, off, e, dict(POL, theta_max_deg=theta, theta_min_deg=theta)))
+
+
 def test_rejects_bad_arguments(mb):
     d, off, e = synth.detections(9, 2, count=(3, 5))
     L = mb.load()
