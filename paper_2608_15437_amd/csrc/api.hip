@@ -52,7 +52,7 @@ mmbev_status_t cc_plan(const mmbev_grid_t* g, const mmbev_cluster_params_t* prm,
   p->off_occ = off;
   off += align256((size_t)p->nwords * 8);  // occ, then rootbits
   p->off_wpre = off;
-  off += align256((size_t)p->nwords * 4);
+  off += align256((size_t)p->nwords / 16 * 4);
   p->off_bsum = off;
   off += align256((size_t)p->nblocks * 4);
   p->off_parent = off;

@@ -19,7 +19,10 @@ namespace {
 
 constexpr int32_t kCcNone = -1;               // row outside the band or invalid
 constexpr uint32_t kCcFollower = 0x80000000u;  // row whose cell another row owns
-constexpr int kCcWords = kBlock * 16;          // bitmap words per scan block
+constexpr int kCcGroup = 16;                   // bitmap words per group (64 bytes: one line)
+constexpr int kCcWords = kBlock * kCcGroup;    // bitmap words per scan block, a group per thread
+constexpr int kCcAccumBlock = 1024;            // threads of an accumulation workgroup
+constexpr int kCcTable = 1024;                 // clusters an accumulation workgroup sums in LDS (power of two)
 
 __device__ __forceinline__ int32_t cc_load(const int32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -84,11 +87,25 @@ __device__ __forceinline__ bool cc_bit(const uint32_t* bits, int32_t cell) {
   return (bits[cell >> 5] >> (cell & 31)) & 1u;
 }
 
-// Kept roots before `cell` (cell <= total cells).
-__device__ __forceinline__ int64_t cc_rank(const CcConfig& c, int64_t cell) {
-  if (cell >= c.cells) return (int64_t)c.hdr->clusters;
-  const uint32_t w = (uint32_t)(cell >> 5);
-  return (int64_t)c.wpre[w] + __popc(c.rootbits[w] & ((1u << (cell & 31)) - 1u));
+// Kept roots before `cell` (cell < total cells): those of the scan blocks
+// before its block (s_blk, in LDS), of the block's word groups before its
+// group, and of the group's words up to the cell (one 64-byte line).
+__device__ __forceinline__ uint32_t cc_rank(const CcConfig& c, const uint32_t* s_blk, int64_t cell) {
+  const uint32_t w = (uint32_t)(cell >> 5), g = w / kCcGroup, in = w % kCcGroup;
+  const uint4* line = reinterpret_cast<const uint4*>(c.rootbits + g * kCcGroup);
+  uint32_t rank = s_blk[w / kCcWords] + c.wpre[g];
+#pragma unroll
+  for (uint32_t k = 0; k < kCcGroup / 4; ++k) {
+    const uint4 v = line[k];
+    const uint32_t x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) {
+      const uint32_t j = 4 * k + u;
+      const uint32_t m = j < in ? ~0u : j == in ? (1u << (cell & 31)) - 1u : 0u;
+      rank += __popc(x[u] & m);
+    }
+  }
+  return rank;
 }
 
 __device__ __forceinline__ int64_t cc_rows(const CcConfig& c) {
@@ -127,9 +144,11 @@ __device__ __forceinline__ T run_suffix(T v, const WaveRun& w, Op op) {
   return v;
 }
 
+// Both bitmaps (adjacent), 16 bytes per thread: for 33 MB each 4-byte stores
+// took 18 us, these take 10.
 __global__ __launch_bounds__(kBlock) void cc_clear_kernel(CcConfig c) {
   const uint64_t g = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (g < 2 * (uint64_t)c.nwords) c.occ[g] = 0u;  // occ and rootbits are adjacent
+  if (g < 2 * (uint64_t)c.nwords / 4) reinterpret_cast<uint4*>(c.occ)[g] = make_uint4(0u, 0u, 0u, 0u);
   if (g == 0) {
     c.hdr->fault = 0;
     c.hdr->clusters = 0;
@@ -195,11 +214,35 @@ __global__ __launch_bounds__(kBlock) void cc_mark_kernel(CcConfig c) {
   if (bad) atomicOr(&c.hdr->fault, MMBEV_FAULT_VOXELS);
 }
 
+// The first occupied cell of x's horizontal run inside its bitmap word and
+// its lattice row: x's component's, and at most x.
+__device__ __forceinline__ int32_t cc_run_start(const CcConfig& c, int32_t x, int32_t col) {
+  const uint32_t bit = (uint32_t)x & 31u;
+  const uint32_t gaps = ~c.occ[x >> 5] & ((1u << bit) - 1u);  // empty cells before x in the word
+  const uint32_t start = gaps ? 32u - (uint32_t)__builtin_clz(gaps) : 0u;
+  return x - (int32_t)min(bit - start, (uint32_t)col);
+}
+
+// u's first join, to the run of its occupied neighbour n (n < u, in column
+// col): u is nearly always still its own root, and one compare-and-swap links
+// it, without walking the two trees first.  (The kernel: one frame of 21,421
+// rows 36 -> 27 us, 128 frames 66 -> 58 us; what is left are the walks of the
+// second joins, a device-wide round trip per step.)
+__device__ __forceinline__ void cc_link(const CcConfig& c, int32_t u, int32_t n, int32_t col) {
+  const int32_t t = cc_run_start(c, n, col);
+  int32_t expected = u;
+  if (!__hip_atomic_compare_exchange_strong(c.parent + u, &expected, t, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT))
+    cc_union(c.parent, u, t);
+}
+
 // Each occupied cell joins its occupied neighbours that come before it
 // (left d, and the row above: a b c left to right), so every edge is taken
 // once.  With 8 neighbours some joins are implied by the others' own joins:
 // b touches a, c and d, so b alone suffices; without b, d touches a, so d
-// and c; without b and d, a and c.  At most two joins per cell.
+// and c; without b and d, a and c.  With 4 neighbours d is implied by b and
+// a (a touches both b and d).  At most two joins per cell, and the first is a
+// link.
 __global__ __launch_bounds__(kBlock) void cc_hook_kernel(CcConfig c) {
   const int64_t V = cc_rows(c);
   const int64_t stride = (int64_t)gridDim.x * kBlock;
@@ -211,21 +254,21 @@ __global__ __launch_bounds__(kBlock) void cc_hook_kernel(CcConfig c) {
     const int32_t up = u - c.Wx;
     const bool d = x > 0 && cc_bit(c.occ, u - 1);
     const bool b = y > 0 && cc_bit(c.occ, up);
+    const bool a = y > 0 && x > 0 && cc_bit(c.occ, up - 1);
     if (c.conn == 4) {
-      if (d) cc_union(c.parent, u, u - 1);
-      if (b) cc_union(c.parent, u, up);
+      if (b) cc_link(c, u, up, x);
+      if (d && !b) cc_link(c, u, u - 1, x - 1);
+      if (d && b && !a) cc_union(c.parent, u, u - 1);
       continue;
     }
-    const bool a = y > 0 && x > 0 && cc_bit(c.occ, up - 1);
     const bool cc = y > 0 && x + 1 < c.Wx && cc_bit(c.occ, up + 1);
     if (b) {
-      cc_union(c.parent, u, up);
-    } else {
-      if (d)
-        cc_union(c.parent, u, u - 1);
-      else if (a)
-        cc_union(c.parent, u, up - 1);
+      cc_link(c, u, up, x);
+    } else if (d || a) {
+      cc_link(c, u, d ? u - 1 : up - 1, x - 1);
       if (cc) cc_union(c.parent, u, up + 1);
+    } else if (cc) {
+      cc_link(c, u, up + 1, x + 1);
     }
   }
 }
@@ -258,98 +301,59 @@ __global__ __launch_bounds__(kBlock) void cc_roots_kernel(CcConfig c) {
   }
 }
 
-// Kept roots per block of kCcWords bitmap words.
+// Kept roots per block of kCcWords bitmap words, and inside a block before
+// each group of kCcGroup words.  (A prefix per word would be another pass over
+// the bitmap and as many bytes written; only the roots' ranks are ever taken.)
 __global__ __launch_bounds__(kBlock) void cc_blocksum_kernel(CcConfig c) {
   __shared__ uint32_t s_tmp[kWaves];
-  const uint32_t w0 = blockIdx.x * kCcWords + threadIdx.x * 16;
+  const uint32_t w0 = blockIdx.x * kCcWords + threadIdx.x * kCcGroup;
   uint32_t sum = 0;
+  if (w0 < c.nwords) {  // nwords is a multiple of kCcGroup
 #pragma unroll
-  for (int k = 0; k < 16; k += 4) {
-    if (w0 + k + 3 < c.nwords) {
+    for (int k = 0; k < kCcGroup; k += 4) {
       const uint4 v = *reinterpret_cast<const uint4*>(c.rootbits + w0 + k);
       sum += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
-    } else {
-      for (int j = 0; j < 4; ++j)
-        if (w0 + k + j < c.nwords) sum += __popc(c.rootbits[w0 + k + j]);
     }
   }
   uint32_t total;
-  block_exclusive_scan(sum, s_tmp, total);
+  const uint32_t ex = block_exclusive_scan(sum, s_tmp, total);
+  if (w0 < c.nwords) c.wpre[w0 / kCcGroup] = ex;
   if (threadIdx.x == 0) c.bsum[blockIdx.x] = total;
 }
 
-// One workgroup: exclusive prefix of the block sums (at most kCcWords blocks)
-// and the number of clusters.
-__global__ __launch_bounds__(kBlock) void cc_blockscan_kernel(CcConfig c) {
-  __shared__ uint32_t s_tmp[kWaves];
-  const uint32_t i0 = threadIdx.x * 16;
-  uint32_t v[16], sum = 0;
-#pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    v[k] = i0 + k < c.nblocks ? c.bsum[i0 + k] : 0u;
-    sum += v[k];
-  }
-  uint32_t total;
-  uint32_t ex = block_exclusive_scan(sum, s_tmp, total);
-#pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    if (i0 + k < c.nblocks) c.bsum[i0 + k] = ex;
-    ex += v[k];
-  }
-  if (threadIdx.x == 0) c.hdr->clusters = total;
-}
-
-// Per-word exclusive prefix of kept roots.
-__global__ __launch_bounds__(kBlock) void cc_wordpre_kernel(CcConfig c) {
-  __shared__ uint32_t s_tmp[kWaves];
-  const uint32_t w0 = blockIdx.x * kCcWords + threadIdx.x * 16;
-  uint32_t pc[16], sum = 0;
-#pragma unroll
-  for (int k = 0; k < 16; k += 4) {
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (w0 + k + 3 < c.nwords) {
-      v = *reinterpret_cast<const uint4*>(c.rootbits + w0 + k);
-    } else {
-      if (w0 + k < c.nwords) v.x = c.rootbits[w0 + k];
-      if (w0 + k + 1 < c.nwords) v.y = c.rootbits[w0 + k + 1];
-      if (w0 + k + 2 < c.nwords) v.z = c.rootbits[w0 + k + 2];
-    }
-    pc[k] = __popc(v.x);
-    pc[k + 1] = __popc(v.y);
-    pc[k + 2] = __popc(v.z);
-    pc[k + 3] = __popc(v.w);
-    sum += pc[k] + pc[k + 1] + pc[k + 2] + pc[k + 3];
-  }
-  uint32_t total;
-  uint32_t ex = block_exclusive_scan(sum, s_tmp, total) + c.bsum[blockIdx.x];
-#pragma unroll
-  for (int k = 0; k < 16; k += 4) {
-    uint4 o;
-    o.x = ex;
-    o.y = ex + pc[k];
-    o.z = o.y + pc[k + 1];
-    o.w = o.z + pc[k + 2];
-    ex = o.w + pc[k + 3];
-    if (w0 + k + 3 < c.nwords) {
-      *reinterpret_cast<uint4*>(c.wpre + w0 + k) = o;
-    } else {
-      if (w0 + k < c.nwords) c.wpre[w0 + k] = o.x;
-      if (w0 + k + 1 < c.nwords) c.wpre[w0 + k + 1] = o.y;
-      if (w0 + k + 2 < c.nwords) c.wpre[w0 + k + 2] = o.z;
-    }
-  }
-}
-
 // Cluster rows of the kept roots (their fixed fields, and the identities of
-// the box, sums and counts accumulated next), and the frame offsets.
+// the box, sums and counts accumulated next), and the frame offsets.  Every
+// workgroup scans the block sums itself (at most kCcWords of them, 16 KB from
+// L2).  A root's count word then holds its cluster index (-1: not kept),
+// which the accumulation reads instead of ranking the root for every row.
 __global__ __launch_bounds__(kBlock) void cc_init_kernel(CcConfig c) {
+  __shared__ uint32_t s_tmp[kWaves];
+  __shared__ uint32_t s_blk[kCcWords];
   const int64_t V = cc_rows(c);
   const int64_t stride = (int64_t)gridDim.x * kBlock;
   const int64_t g0 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  for (int64_t b = g0; b <= c.B; b += stride) c.out_off[b] = cc_rank(c, b * (int64_t)c.ncell);
+  uint32_t carry = 0;
+  for (uint32_t base = 0; base < c.nblocks; base += kBlock) {
+    const uint32_t i = base + threadIdx.x;
+    const uint32_t v = i < c.nblocks ? c.bsum[i] : 0u;
+    uint32_t total;
+    const uint32_t ex = block_exclusive_scan(v, s_tmp, total);
+    s_blk[i] = carry + ex;
+    carry += total;
+  }
+  __syncthreads();
+  if (g0 == 0) c.hdr->clusters = carry;
+  for (int64_t b = g0; b <= c.B; b += stride) {
+    const int64_t cell = b * (int64_t)c.ncell;
+    c.out_off[b] = cell >= c.cells ? (int64_t)carry : (int64_t)cc_rank(c, s_blk, cell);
+  }
   for (int64_t r = g0; r < V; r += stride) {
     const int32_t u = c.rcell[r];
-    if (u < 0 || c.parent[u] != u || !cc_bit(c.rootbits, u)) continue;
+    if (u < 0 || c.parent[u] != u) continue;
+    if (!cc_bit(c.rootbits, u)) {
+      c.cnt[u] = -1;
+      continue;
+    }
     mmbev_cluster_t o;
     o.frame = u / c.ncell;
     o.root = u % c.ncell;
@@ -360,26 +364,72 @@ __global__ __launch_bounds__(kBlock) void cc_init_kernel(CcConfig c) {
     o.x1 = o.y1 = -1;
     o.reserved = 0;
     o.sum_x = o.sum_y = 0;
-    c.out[cc_rank(c, u)] = o;
+    const uint32_t id = cc_rank(c, s_blk, u);
+    c.out[id] = o;
+    c.cnt[u] = (int32_t)id;
   }
 }
 
+// What a run of rows adds to its cluster.
+struct CcAdd {
+  int32_t voxels, points, x0, y0, x1, y1;
+  unsigned long long sx, sy;
+};
+
+__device__ __forceinline__ void cc_add(mmbev_cluster_t* o, const CcAdd& a) {
+  atomicAdd(&o->voxels, a.voxels);
+  atomicAdd(&o->points, a.points);
+  if (a.x1 >= 0) {  // some row owns its cell
+    atomicMin(&o->x0, a.x0);
+    atomicMin(&o->y0, a.y0);
+    atomicMax(&o->x1, a.x1);
+    atomicMax(&o->y1, a.y1);
+    atomicAdd(reinterpret_cast<unsigned long long*>(&o->sum_x), a.sx);
+    atomicAdd(reinterpret_cast<unsigned long long*>(&o->sum_y), a.sy);
+  }
+}
+
+// The clusters an accumulation workgroup meets, summed in LDS: entry e holds
+// cluster key[e] (-1: free).
+struct CcTable {
+  int32_t key[kCcTable];
+  int32_t voxels[kCcTable], points[kCcTable], x0[kCcTable], y0[kCcTable], x1[kCcTable], y1[kCcTable];
+  unsigned long long sx[kCcTable], sy[kCcTable];
+};
+
 // Labels of the rows, voxel and point counts; each cell (its owning row)
-// adds itself to its cluster's box and sums.
-__global__ __launch_bounds__(kBlock) void cc_accum_kernel(CcConfig c) {
+// adds itself to its cluster's box and sums.  A workgroup takes one
+// contiguous part of the rows and sums it per cluster in LDS first: atomics
+// on one cluster's line serialise, and a cluster's rows come once per layer,
+// many short runs each.  A frame's clusters have consecutive indices, so the
+// table's first place is free or the cluster's own unless the part holds
+// more than kCcTable clusters; a run that finds no place in a few steps goes
+// to memory.  (One frame of 21,421 rows with one large cluster 48 -> 9 us;
+// 128 frames, 903,061 rows, 106 -> 29 us.)
+__global__ __launch_bounds__(kCcAccumBlock) void cc_accum_kernel(CcConfig c) {
+  __shared__ CcTable T;
+  const int tid = threadIdx.x;
   const int64_t V = cc_rows(c);
-  const int64_t stride = (int64_t)gridDim.x * kBlock;
-  const int64_t g0 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  for (int64_t base = g0 - (int64_t)__lane_id(); base < V; base += stride) {
-    const int64_t r = base + (int64_t)__lane_id();
-    const int32_t rc = r < V ? c.rcell[r] : kCcNone;
+  const int64_t part = ((V + gridDim.x - 1) / gridDim.x + kCcAccumBlock - 1) / kCcAccumBlock * kCcAccumBlock;
+  const int64_t lo = (int64_t)blockIdx.x * part, hi = min(lo + part, V);
+  if (lo >= V) return;  // uniform
+  for (int e = tid; e < kCcTable; e += kCcAccumBlock) {
+    T.key[e] = -1;
+    T.voxels[e] = T.points[e] = 0;
+    T.x0[e] = T.y0[e] = INT32_MAX;
+    T.x1[e] = T.y1[e] = -1;
+    T.sx[e] = T.sy[e] = 0ull;
+  }
+  __syncthreads();
+  for (int64_t base = lo; base < hi; base += kCcAccumBlock) {
+    const int64_t r = base + tid;
+    const int32_t rc = r < hi ? c.rcell[r] : kCcNone;
     int32_t id = -1, x = 0, y = 0, pts = 0;
     bool cell_owner = false;
     if (rc != kCcNone) {
       const int32_t u = (int32_t)((uint32_t)rc & ~kCcFollower);
-      const int32_t root = cc_root(c.parent, u);
-      if (cc_bit(c.rootbits, root)) {
-        id = (int32_t)cc_rank(c, root);
+      id = c.cnt[cc_root(c.parent, u)];
+      if (id >= 0) {
         pts = c.counts[r];
         cell_owner = rc >= 0;
         const int32_t local = u % c.ncell;
@@ -387,49 +437,66 @@ __global__ __launch_bounds__(kBlock) void cc_accum_kernel(CcConfig c) {
         y = local / c.Wx;
       }
     }
-    if (r < V) c.labels[r] = id;
+    if (r < hi) c.labels[r] = id;
     // runs of lanes of one cluster: one set of atomics per run; the box and
     // sums take each cell once (its owning row)
     const WaveRun w = wave_run(__shfl_up(id, 1, 64) != id);
-    const int32_t points = run_suffix(pts, w, [](int32_t a, int32_t b) { return a + b; });
-    const int32_t x0 = run_suffix(cell_owner ? x : INT32_MAX, w, [](int32_t a, int32_t b) { return min(a, b); });
-    const int32_t y0 = run_suffix(cell_owner ? y : INT32_MAX, w, [](int32_t a, int32_t b) { return min(a, b); });
-    const int32_t x1 = run_suffix(cell_owner ? x : -1, w, [](int32_t a, int32_t b) { return max(a, b); });
-    const int32_t y1 = run_suffix(cell_owner ? y : -1, w, [](int32_t a, int32_t b) { return max(a, b); });
-    const int64_t sx = run_suffix((int64_t)(cell_owner ? x : 0), w, [](int64_t a, int64_t b) { return a + b; });
-    const int64_t sy = run_suffix((int64_t)(cell_owner ? y : 0), w, [](int64_t a, int64_t b) { return a + b; });
+    CcAdd a;
+    a.voxels = (int32_t)(w.end - w.start + 1);
+    a.points = run_suffix(pts, w, [](int32_t p, int32_t q) { return p + q; });
+    a.x0 = run_suffix(cell_owner ? x : INT32_MAX, w, [](int32_t p, int32_t q) { return min(p, q); });
+    a.y0 = run_suffix(cell_owner ? y : INT32_MAX, w, [](int32_t p, int32_t q) { return min(p, q); });
+    a.x1 = run_suffix(cell_owner ? x : -1, w, [](int32_t p, int32_t q) { return max(p, q); });
+    a.y1 = run_suffix(cell_owner ? y : -1, w, [](int32_t p, int32_t q) { return max(p, q); });
+    // a wave's column sums fit 32 bits (64 columns below 2^24)
+    a.sx = run_suffix((uint32_t)(cell_owner ? x : 0), w, [](uint32_t p, uint32_t q) { return p + q; });
+    a.sy = run_suffix((uint32_t)(cell_owner ? y : 0), w, [](uint32_t p, uint32_t q) { return p + q; });
     if (id >= 0 && w.lane == w.start) {
-      mmbev_cluster_t* o = c.out + id;
-      atomicAdd(&o->voxels, (int32_t)(w.end - w.start + 1));
-      atomicAdd(&o->points, points);
-      if (x1 >= 0) {  // some row of the run owns its cell
-        atomicMin(&o->x0, x0);
-        atomicMin(&o->y0, y0);
-        atomicMax(&o->x1, x1);
-        atomicMax(&o->y1, y1);
-        atomicAdd(reinterpret_cast<unsigned long long*>(&o->sum_x), (unsigned long long)sx);
-        atomicAdd(reinterpret_cast<unsigned long long*>(&o->sum_y), (unsigned long long)sy);
+      uint32_t e = (uint32_t)id & (kCcTable - 1);
+      bool found = false;
+      for (int probe = 0; probe < 4 && !found; ++probe) {
+        const int32_t old = atomicCAS(&T.key[e], -1, id);
+        found = old == -1 || old == id;
+        if (!found) e = (e + 1) & (kCcTable - 1);
+      }
+      if (found) {
+        atomicAdd(&T.voxels[e], a.voxels);
+        atomicAdd(&T.points[e], a.points);
+        if (a.x1 >= 0) {
+          atomicMin(&T.x0[e], a.x0);
+          atomicMin(&T.y0[e], a.y0);
+          atomicMax(&T.x1[e], a.x1);
+          atomicMax(&T.y1[e], a.y1);
+          atomicAdd(&T.sx[e], a.sx);
+          atomicAdd(&T.sy[e], a.sy);
+        }
+      } else {
+        cc_add(c.out + id, a);
       }
     }
   }
+  __syncthreads();
+  for (int e = tid; e < kCcTable; e += kCcAccumBlock)
+    if (T.key[e] >= 0)
+      cc_add(c.out + T.key[e], CcAdd{T.voxels[e], T.points[e], T.x0[e], T.y0[e], T.x1[e], T.y1[e], T.sx[e], T.sy[e]});
 }
 
 }  // namespace
 
 hipError_t launch_clusters(const CcConfig& c, hipStream_t st) {
-  const uint32_t clear_grid = (uint32_t)((2 * (uint64_t)c.nwords + kBlock - 1) / kBlock);
+  const uint32_t clear_grid = (uint32_t)((2 * (uint64_t)c.nwords / 4 + kBlock - 1) / kBlock);
   const uint64_t need = (uint64_t)std::max<int64_t>(c.rows, (int64_t)c.B + 1);
-  const dim3 rows_grid((uint32_t)std::min<uint64_t>((need + kBlock - 1) / kBlock, kCcRowGrid)), block(kBlock);
+  const uint64_t blocks = (need + kBlock - 1) / kBlock;
+  const dim3 rows_grid((uint32_t)std::min<uint64_t>(blocks, kCcRowGrid)), block(kBlock);
   hipLaunchKernelGGL(cc_clear_kernel, dim3(std::max(clear_grid, 1u)), block, 0, st, c);
   hipLaunchKernelGGL(cc_mark_kernel, rows_grid, block, 0, st, c);
   hipLaunchKernelGGL(cc_hook_kernel, rows_grid, block, 0, st, c);
   hipLaunchKernelGGL(cc_compress_kernel, rows_grid, block, 0, st, c);
   hipLaunchKernelGGL(cc_roots_kernel, rows_grid, block, 0, st, c);
   hipLaunchKernelGGL(cc_blocksum_kernel, dim3(c.nblocks), block, 0, st, c);
-  hipLaunchKernelGGL(cc_blockscan_kernel, dim3(1), block, 0, st, c);
-  hipLaunchKernelGGL(cc_wordpre_kernel, dim3(c.nblocks), block, 0, st, c);
-  hipLaunchKernelGGL(cc_init_kernel, rows_grid, block, 0, st, c);
-  hipLaunchKernelGGL(cc_accum_kernel, rows_grid, block, 0, st, c);
+  hipLaunchKernelGGL(cc_init_kernel, dim3((uint32_t)std::min<uint64_t>(blocks, kCcInitGrid)), block, 0, st, c);
+  const uint64_t parts = (need + kCcAccumBlock - 1) / kCcAccumBlock;
+  hipLaunchKernelGGL(cc_accum_kernel, dim3((uint32_t)std::min<uint64_t>(parts, kCcAccumGrid)), dim3(kCcAccumBlock), 0, st, c);
   return hipGetLastError();
 }
 

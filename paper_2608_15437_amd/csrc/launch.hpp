@@ -42,6 +42,8 @@ struct CcHeader {
 };
 
 constexpr uint32_t kCcRowGrid = 8192;     // workgroups of the per-row launches (they loop)
+constexpr uint32_t kCcInitGrid = 1024;    // ... of the launch whose workgroups each scan the block sums (four per CU)
+constexpr uint32_t kCcAccumGrid = 512;    // ... of the accumulation (1,024 threads: two per CU)
 constexpr int64_t kCcMaxCells = (int64_t)1 << 29;  // cells over all frames (single-workgroup block scan)
 
 struct CcConfig {
@@ -54,10 +56,10 @@ struct CcConfig {
   CcHeader* hdr;
   uint32_t* occ;            // [nwords] occupied cells; rootbits follows it directly
   uint32_t* rootbits;       // [nwords] roots of kept components
-  uint32_t* wpre;           // [nwords] kept roots in the words before
+  uint32_t* wpre;           // [nwords / 16] kept roots before a 16-word group in its scan block
   uint32_t* bsum;           // [nblocks]
   int32_t* parent;          // [cells], valid at occupied cells only
-  int32_t* cnt;             // [cells], valid at occupied cells only
+  int32_t* cnt;             // [cells], valid at occupied cells only; a root's becomes its cluster index (-1: not kept)
   int32_t* rcell;           // [rows] the row's cell (top bit: another row owns it), or -1
   int64_t rows;             // B * max_voxels
   int64_t cells;            // B * ncell

@@ -102,6 +102,23 @@ def test_random_grids_match_oracle(gpu_lib, conn, seed, shapes, density, shift, 
     _same(res, exp, f"seed{seed}")
 
 
+@pytest.mark.parametrize("side,layers,conn,frames", [(250, 2, 4, 1), (64, 3, 4, 3), (97, 2, 8, 2)])
+def test_many_small_clusters(gpu_lib, side, layers, conn, frames):
+    """A checkerboard in several layers: single-cell clusters (one diagonal net with 8 neighbours), their rows spread
+    over the layers; more clusters than an accumulation workgroup sums in LDS, with colliding places where a layer's
+    last rows and the next one's first lie in one workgroup's part, and ranks across many bitmap words and groups."""
+    occ = (np.add.outer(np.arange(side), np.arange(side)) % 2) == 0
+    y, x = np.nonzero(occ)
+    one = np.concatenate([np.stack([np.zeros_like(x), np.full_like(x, z), y, x], 1) for z in range(layers)])
+    coords = np.concatenate([one + [[f, 0, 0, 0]] for f in range(frames)]).astype(np.int32)
+    counts = (np.arange(len(coords)) % 9 + 1).astype(np.int32)
+    voff = np.arange(frames + 1) * len(one)
+    dims = (side, side, layers)
+    res, p = _gpu(gpu_lib, coords, counts, voff, dims, frames, len(one), gpu_lib.cluster_params(0, layers, 0, conn, 1))
+    assert p.fault() == 0
+    _same(res, oracle.clusters(coords, counts, voff, dims, frames, 0, layers, 0, conn, 1), f"side {side}")
+
+
 def test_one_giant_component_and_a_serpentine(gpu_lib):
     """A fully occupied 1024 x 1024 frame (one cluster of 2^20 cells) and a serpentine path (long chains)."""
     full = np.ones((1024, 1024), bool)
