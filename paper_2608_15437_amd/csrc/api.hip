@@ -377,6 +377,16 @@ mmbev_status_t voxelize(const mmbev_points_t* points, const uint8_t* sweep_ids, 
   const int32_t lds_words = c.lds_wmask >= 0 ? c.lds_wmask + p.ncells * p.W : c.lds_cell + c.lds_cell_cap;
   c.lds_dyn_bytes = (int32_t)(((size_t)lds_words * 4 + 15) / 16 * 16);
   c.small_call = p.fchunk_max <= kSmallChunks;
+  // small calls of a few frames count each radix pass's digits where its
+  // pairs are written: rows for every chunk a frame can have (half tiles, at
+  // most kMaxFrameChunks), as long as they fit the space of hpos and hplace
+  // (from about 2,000 points on)
+  {
+    const int64_t rows = std::min<int64_t>(kMaxFrameChunks, N / (kSortTile / 2) + 1);
+    const bool fold = c.small_call && p.B <= kFoldFrames && (int64_t)p.passes * p.B * rows * kSortBins <= 2 * N;
+    c.fold_rows = fold ? (int32_t)rows : 0;
+    c.fold_cnt = c.hpos;
+  }
   c.schunk_max = (int32_t)p.schunk_max;
   c.vtile_max = (int32_t)p.vtile_max;
   c.mean_grid = (int32_t)p.mean_grid;

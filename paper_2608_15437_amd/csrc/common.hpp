@@ -27,6 +27,7 @@ constexpr int kMaxLdsRois = 256;      // ROI records of one filter workgroup sta
 constexpr int kMaxLdsBudgetWords = 256;
 constexpr int kMaxPoseLds = 64;       // (frame, sweep) poses of one filter workgroup staged in LDS
 constexpr int kSmallChunks = 2048;  // calls of at most this many filter chunks need no segments launch
+constexpr int kFoldFrames = 8;      // frames of a call whose radix passes have no count launch, at most
 constexpr int kFuseFrames = kBlock - 1;  // frames of a call whose point filter lays out the call itself (one per thread)
 constexpr int kFuseWideFrames = 16;    // ... and with several ROI words per cell, at most this many frames
 constexpr int kFuseWordCap = 8192;     // ... whose cells' ROI words (cells x words) fit this many LDS words
@@ -103,6 +104,7 @@ struct Config {
   int32_t kb, passes, dbits;
   int32_t vec;  // 16-byte vector loads allowed
   int32_t fuse_stage;  // the point filter lays out the call and builds its frame's tables (no staging kernel)
+  int32_t fold_rows;   // rows per frame of fold_cnt; 0: every radix pass has a count launch of its own
   int32_t small_call;  // at most kSmallChunks filter chunks: the compaction launch does the segments kernel's work
   // out-of-ROI keep (Alg. 1 rate rho_out): threshold round(rho_out * 2^24)
   // on the top 24 bits of the point's SplitMix64 draw; 0 keeps none
@@ -132,6 +134,11 @@ struct Config {
   uint4* schunk;           // [schunk_max] pair chunk k: (first pair, end, frame, first pair of the frame)
   uint2* schunk_frame;     // [schunk_max] pair chunk k: its frame's chunks [x, y)
   uint32_t* cnt;           // [schunk_max][kSortBins] digit counts of chunk k in a pass
+  // calls whose radix passes have no count launch: [passes][B][fold_rows]
+  // count rows (chunk j of frame b in a pass), cleared by the point filter,
+  // counted with atomics by the launch that writes the pass's pairs (it lies
+  // over hpos and hplace, which are written after the sort)
+  uint32_t* fold_cnt;
   uint4* vtile;            // [vtile_max] voxel tile t: (first pair, end, frame, first pair of the frame)
   uint32_t* vt_first;      // [B+1] first voxel tile of frame b
   uint32_t* hcount;        // [vtile_max] voxels (heads) of tile t

@@ -908,6 +908,12 @@ __global__ __launch_bounds__(kBlock, 5) void filter_kernel(Config c) {
   }
   __syncthreads();
 
+  if (c.fold_rows) {  // uniform: the radix passes' count rows cleared, 16 bytes per thread and step
+    static_assert(kSortBins % 4 == 0, "16-byte stores");
+    uint4* z = reinterpret_cast<uint4*>(c.fold_cnt);
+    const uint32_t n4 = (uint32_t)c.passes * (uint32_t)c.B * (uint32_t)c.fold_rows * (kSortBins / 4);
+    for (uint32_t i = blockIdx.x * kBlock + tid; i < n4; i += gridDim.x * kBlock) z[i] = make_uint4(0u, 0u, 0u, 0u);
+  }
   if (k >= nchunks || (FS && !pl.staged)) return;
   WaveRun wr{0u, 0u, 0u, lo, b, k};
   if (staged)

@@ -61,6 +61,35 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t dig, bool valid) {
   return __ballot(valid) & ~(((uint64_t)dhi << 32) | dlo);
 }
 
+// A pair's chunk from its place in the frame: chunks of `pairs` pairs (a
+// uniform value, mostly a power of two; a division costs a lone wave more).
+__device__ __forceinline__ uint32_t chunk_of_place(uint32_t place, uint32_t pairs) {
+  return (pairs & (pairs - 1u)) == 0u ? place >> __builtin_ctz(pairs) : place / pairs;
+}
+
+// One count of digit dig in chunk j's row of `rows` for every lane with ok
+// set.  Lanes of a wave with the same chunk (neighbours: a wave's pairs go to
+// ascending places) and digit are counted by one atomic: atomics on one
+// address serialise (without the matching a frame that keeps 250,000 points
+// took 122 us per call instead of 112).  Every lane of the wave must call it.
+__device__ __forceinline__ void fold_count(uint32_t* rows, uint32_t j, uint32_t dig, bool ok) {
+  const uint32_t lane = __lane_id();
+  const uint32_t jj = ok ? j : 0xffffffffu;
+  const uint32_t pj = (uint32_t)__shfl_up((int)jj, 1, 64);
+  const uint64_t H = __ballot(lane == 0 || pj != jj);  // first lanes of the runs of one chunk
+  const uint32_t start = 63u - (uint32_t)__builtin_clzll(H & ((2ull << lane) - 1ull));  // wraps to all ones for lane 63
+  const uint64_t above = lane == 63 ? 0ull : H & (~0ull << (lane + 1));
+  const uint64_t run = (above ? (1ull << __builtin_ctzll(above)) - 1ull : ~0ull) & (~0ull << start);
+  const uint64_t same = match_digit(dig, ok) & run;
+  if (ok && count_below(same) == 0)
+    __hip_atomic_fetch_add(&rows[j * kSortBins + dig], (uint32_t)__popcll(same), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The fold_cnt rows of frame b in a pass.
+__device__ __forceinline__ uint32_t* fold_rows_of(const Config& c, int pass, uint32_t b) {
+  return c.fold_cnt + (size_t)((uint32_t)pass * (uint32_t)c.B + b) * (uint32_t)c.fold_rows * kSortBins;
+}
+
 constexpr int kSegBlock = 1024;  // threads of the segments kernel
 constexpr int kSegWaves = kSegBlock / 64;
 constexpr int kSegLdsFrames = 4096;  // frame starts kept in LDS up to this many frames
@@ -251,23 +280,26 @@ __global__ __launch_bounds__(kSegBlock) void segments_kernel(Config c) {
   segments_body<kLds, kSegBlock>(c, s_tmp, s_fstart, s_sfirst, s_tfirst, s_pre, &s_most);
 }
 
-// Sums of three values over the workgroup (s_tmp: 3 * WAVES words).
+// Sums of four values over the workgroup (s_tmp: 4 * WAVES words).
 template <int WAVES>
-__device__ __forceinline__ uint3 block_sum3(uint32_t a, uint32_t b, uint32_t d, uint32_t* s_tmp) {
+__device__ __forceinline__ uint4 block_sum4(uint32_t a, uint32_t b, uint32_t d, uint32_t e, uint32_t* s_tmp) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t xa = wave_inclusive_sum(a), xb = wave_inclusive_sum(b), xd = wave_inclusive_sum(d);
+  const uint32_t xa = wave_inclusive_sum(a), xb = wave_inclusive_sum(b), xd = wave_inclusive_sum(d),
+                 xe = wave_inclusive_sum(e);
   if (lane == 63) {
     s_tmp[wave] = xa;
     s_tmp[WAVES + wave] = xb;
     s_tmp[2 * WAVES + wave] = xd;
+    s_tmp[3 * WAVES + wave] = xe;
   }
   __syncthreads();
-  uint3 t = make_uint3(0u, 0u, 0u);
+  uint4 t = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
   for (int w = 0; w < WAVES; ++w) {
     t.x += s_tmp[w];
     t.y += s_tmp[WAVES + w];
     t.z += s_tmp[2 * WAVES + w];
+    t.w += s_tmp[3 * WAVES + w];
   }
   __syncthreads();
   return t;
@@ -302,7 +334,7 @@ __global__ __launch_bounds__(kCompactBlock) void compact_kernel(Config c, uint32
   static_assert(kChunkWords <= kCompactBlock, "one bitmap word per thread");
   extern __shared__ float s_pose[];  // [S][12]
   __shared__ uint16_t s_list[kMaxChunkPoints];  // kept point offsets in the chunk, ascending
-  __shared__ uint32_t s_tmp[3 * kCompactWaves];
+  __shared__ uint32_t s_tmp[4 * kCompactWaves];
   __shared__ unsigned long long s_most;
   const int tid = threadIdx.x;
   if (kSmall && blockIdx.x == gridDim.x - 1) {  // uniform: the segments kernel's work
@@ -355,6 +387,9 @@ __global__ __launch_bounds__(kCompactBlock) void compact_kernel(Config c, uint32
   const uint32_t n = min(total, cnt);  // equal unless the workspace was corrupted
   uint32_t pi[kCompactItems], sw[kCompactItems];
   float v[kCompactItems][8];
+  uint32_t chunk_pairs = 1;  // pairs per chunk of the frame in the radix passes (when the first pass is counted here)
+  const uint32_t digit_mask = (1u << c.dbits) - 1u;
+  uint32_t* fold = kSmall && c.fold_rows ? fold_rows_of(c, 0, (uint32_t)b) : nullptr;
   auto load_batch = [&](uint32_t base) {
 #pragma unroll
     for (int u = 0; u < kCompactItems; ++u) {
@@ -374,6 +409,7 @@ __global__ __launch_bounds__(kCompactBlock) void compact_kernel(Config c, uint32
 #pragma unroll
     for (int u = 0; u < kCompactItems; ++u) {
       const uint32_t t = base + u * kCompactBlock + tid;
+      uint32_t vkey = 0;
       if (t < n) {
         const uint32_t q = dst + t;
         float px, py, pz;
@@ -383,7 +419,8 @@ __global__ __launch_bounds__(kCompactBlock) void compact_kernel(Config c, uint32
                         quantize_axis(py, c.mn[1], c.vs[1], c.Df[1], iy) &&
                         quantize_axis(pz, c.mn[2], c.vs[2], c.Df[2], iz);
         if (!in) raise_fault(c.hdr, MMBEV_FAULT_INTERNAL);  // the filter kept it: never
-        kout[q] = in ? ((uint32_t)iz * c.Dy + (uint32_t)iy) * c.Dx + (uint32_t)ix : 0u;
+        vkey = in ? ((uint32_t)iz * c.Dy + (uint32_t)iy) * c.Dx + (uint32_t)ix : 0u;
+        kout[q] = vkey;
         // the record: 16-byte stores when RW is a multiple of four, else
         // 8-byte stores (records are 8-byte aligned)
         const uint32_t w[10] = {pi[u], __float_as_uint(px), __float_as_uint(py), __float_as_uint(pz),
@@ -401,13 +438,16 @@ __global__ __launch_bounds__(kCompactBlock) void compact_kernel(Config c, uint32
             if (2 * k < RW) reinterpret_cast<uint2*>(rp)[k] = make_uint2(w[2 * k], w[2 * k + 1]);
         }
       }
+      // the first pass's digit counts (frame-relative places fall in the frame's chunks in order)
+      if (kSmall && fold != nullptr && base + u * kCompactBlock < n)  // uniform
+        fold_count(fold, chunk_of_place(dst + t - fs, chunk_pairs), vkey & digit_mask, t < n);
     }
   };
   // the first batch's point loads go out before the poses are stored (the
   // poses' loads were issued before the listing), so the two round trips overlap
   load_batch(0u);
   if (kSmall) {  // kept points of the chunks before k, before the frame's first chunk and before the next frame's
-    uint32_t a0 = 0, a1 = 0, a2 = 0;
+    uint32_t a0 = 0, a1 = 0, a2 = 0, a3 = 0;
 #pragma unroll
     for (int j = 0; j < kSmallItems; ++j) {
       const uint32_t i = (uint32_t)(tid + j * kCompactBlock);
@@ -415,11 +455,13 @@ __global__ __launch_bounds__(kCompactBlock) void compact_kernel(Config c, uint32
       a0 += i < k ? v : 0u;
       a1 += i < ff0 ? v : 0u;
       a2 += i < ff1 ? v : 0u;
+      a3 += v;
     }
-    const uint3 t = block_sum3<kCompactWaves>(a0, a1, a2, s_tmp);
+    const uint4 t = block_sum4<kCompactWaves>(a0, a1, a2, a3, s_tmp);
     dst = t.x;
     fs = t.y;
     fe = t.z;
+    if (c.fold_rows) chunk_pairs = frame_chunk_pairs(fe - fs, chunk_min_tiles(t.w, c.B), half_tile_chunks(t.w, c.B));
   }
 #pragma unroll
   for (int u = 0; u < kPoseRegs; ++u)
@@ -489,6 +531,8 @@ __global__ __launch_bounds__(kBlock) void count_kernel(Config c, int pass, const
   }
 }
 
+constexpr int kSmallRows = 32;  // count rows in flight of a scatter workgroup of a small call
+
 struct ScatterLds {
   uint32_t pos[kSortBins];             // per digit: output position of the tile's pair i of that digit, less i
   uint2 kv[kSortTile];                 // the tile reordered by digit: (key, value)
@@ -515,11 +559,12 @@ __device__ __forceinline__ void load_sort_tile(const uint32_t* kin, const uint32
 // One pair chunk k of the scatter (entries ch, fc), its tiles in the order
 // (wave, round, lane) with NR rounds of 64 per wave: kSortItems, or half of
 // it for a chunk of at most half a tile (every wave busy, half the rounds).
-template <int NR>
+template <int NR, int ROWS, bool FOLD>
 __device__ __forceinline__ void scatter_chunk(const Config& c, ScatterLds& L, int pass, uint32_t k, const uint4 ch,
                                               const uint2 fc, uint32_t K, const uint32_t* kin, const uint32_t* vin,
                                               uint32_t* kout, uint32_t* vout) {
-  constexpr int kRows = 8;  // count rows in flight together
+  constexpr int kGroup = 8;  // rows loaded behind one uniform test
+  static_assert(ROWS % kGroup == 0, "whole groups");
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   WsHeader* h = c.hdr;
@@ -531,15 +576,38 @@ __device__ __forceinline__ void scatter_chunk(const Config& c, ScatterLds& L, in
   const uint32_t lo = ch.x, hi = ch.y;
   uint32_t key[kSortItems], val[kSortItems], nkey[kSortItems], nval[kSortItems];
   if (lo < hi) load_sort_tile<NR>(kin, vin, lo, hi, key, val);
-  // the first kRows count rows of the frame's chunks (at most
+  // the first ROWS count rows of the frame's chunks (at most
   // kMaxFrameChunks rows) go out now and are summed after the first
   // tile is ranked: digit bases = frame start + the frame's smaller
   // digits + this digit in the frame's earlier chunks
-  const uint32_t k0 = fc.x, k1 = max(fc.y, k0);
-  uint2 x[kRows];
+  // (FOLD: row j of the frame's own rows is its chunk j, else row k chunk k)
+  const uint32_t k0 = FOLD ? 0u : fc.x, k1 = max(fc.y, fc.x) - (FOLD ? fc.x : 0u);
+  if (FOLD) k -= fc.x;
+  const uint32_t fb = min(ch.z, (uint32_t)c.B - 1u);
+  const uint32_t* cnt = FOLD ? fold_rows_of(c, pass, fb) : c.cnt;
+  // FOLD: the next pass's digits are counted as the pairs are written, in the
+  // row of the chunk they go to: the frame's chunks have its first one's size
+  uint32_t* next = FOLD && pass + 1 < c.passes ? fold_rows_of(c, pass + 1, fb) : nullptr;
+  uint32_t chunk_pairs = 1;
+  if (FOLD) {
+    const uint4 c0 = c.schunk[fc.x];
+    chunk_pairs = max(c0.y - c0.x, 1u);
+  }
+  uint2 x[ROWS];
+  auto load_rows = [&](uint32_t first) {  // rows first .. first + ROWS of the frame, zeros past its last one
 #pragma unroll
-  for (int u = 0; u < kRows; ++u)
-    x[u] = k0 + u < k1 ? *reinterpret_cast<const uint2*>(c.cnt + (int64_t)(k0 + u) * kSortBins + e0) : make_uint2(0u, 0u);
+    for (int g = 0; g < ROWS; g += kGroup) {
+      if (ROWS == kGroup || first + g < k1) {  // uniform
+#pragma unroll
+        for (int u = g; u < g + kGroup; ++u)
+          x[u] = first + u < k1 ? *reinterpret_cast<const uint2*>(cnt + (int64_t)(first + u) * kSortBins + e0) : make_uint2(0u, 0u);
+      } else {
+#pragma unroll
+        for (int u = g; u < g + kGroup; ++u) x[u] = make_uint2(0u, 0u);
+      }
+    }
+  };
+  load_rows(k0);
   uint32_t run0 = 0, run1 = 0;  // output position of the next pair of digit e0, e0 + 1
   for (uint32_t base = lo; base < hi; base += kSortTile) {
     const bool first = base == lo;
@@ -578,23 +646,24 @@ __device__ __forceinline__ void scatter_chunk(const Config& c, ScatterLds& L, in
     }
     uint32_t ft0 = 0, ft1 = 0, pre0 = 0, pre1 = 0;  // the frame's totals of e0, e1 and their count in earlier chunks
     if (first) {  // uniform
-      for (uint32_t kk = k0;; kk += kRows) {
+      for (uint32_t kk = k0;; kk += ROWS) {
 #pragma unroll
-        for (int u = 0; u < kRows; ++u) {
-          const uint32_t a = d0 ? x[u].x : 0u, b = d1 ? x[u].y : 0u;
-          if (kk + u < k) {
-            pre0 += a;
-            pre1 += b;
+        for (int g = 0; g < ROWS; g += kGroup) {
+          if (ROWS == kGroup || kk + g < k1) {  // uniform
+#pragma unroll
+            for (int u = g; u < g + kGroup; ++u) {
+              const uint32_t a = d0 ? x[u].x : 0u, b = d1 ? x[u].y : 0u;
+              if (kk + u < k) {
+                pre0 += a;
+                pre1 += b;
+              }
+              ft0 += a;
+              ft1 += b;
+            }
           }
-          ft0 += a;
-          ft1 += b;
         }
-        if (kk + kRows >= k1) break;
-#pragma unroll
-        for (int u = 0; u < kRows; ++u) {  // the next rows' loads in flight together
-          const uint32_t kr = kk + kRows + u;
-          x[u] = kr < k1 ? *reinterpret_cast<const uint2*>(c.cnt + (int64_t)kr * kSortBins + e0) : make_uint2(0u, 0u);
-        }
+        if (kk + ROWS >= k1) break;
+        load_rows(kk + ROWS);
       }
     }
     __syncthreads();  // the wave counts are complete
@@ -651,15 +720,22 @@ __device__ __forceinline__ void scatter_chunk(const Config& c, ScatterLds& L, in
 #pragma unroll
     for (int r = 0; r < kSortItems; ++r) {  // unrolled: the LDS reads of all rounds in flight together
       const uint32_t i = (uint32_t)(r * kBlock + tid);
+      uint32_t np = K, nd = 0;
       if (i < n_in) {
         const uint2 kv = L.kv[i];
         const uint32_t gp = L.pos[(kv.x >> shift) & mask] + i;
+        np = gp;
+        if (FOLD && next != nullptr) nd = (kv.x >> (shift + c.dbits)) & mask;
         if (gp < K) {  // always true when the counts match the pairs
           kout[gp] = kv.x;
           vout[gp] = kv.y;
         } else {
           raise_fault(h, MMBEV_FAULT_INTERNAL);
         }
+      }
+      if (FOLD && next != nullptr && (uint32_t)(r * kBlock) < n_in) {  // uniform
+        const uint32_t j = chunk_of_place(np - ch.w, chunk_pairs);
+        fold_count(next, j, nd, np < K && j < k1);
       }
     }
     if (more)
@@ -675,13 +751,32 @@ __device__ __forceinline__ void scatter_chunk(const Config& c, ScatterLds& L, in
 // per-digit step: the count rows (8-byte loads), the tile's digit totals,
 // the scans and the output positions, which it keeps in registers from
 // tile to tile.
-__global__ __launch_bounds__(kBlock, kScatterPerCu) void scatter_kernel(Config c, int pass, const uint32_t* kin, const uint32_t* vin,
+//
+// ROWS count rows of the frame's chunks are in flight together: every batch
+// of them is a round trip of a chunk's first tile.  Eight for large calls,
+// whose workgroups must fit kScatterPerCu to a compute unit and hide each
+// other's trips; 32 for small ones (at most kSmallChunks filter chunks), whose
+// few chunks leave the chip idle, where the registers of the rows cost nothing.
+template <int ROWS, int PER_CU, bool FOLD>
+__global__ __launch_bounds__(kBlock, PER_CU) void scatter_kernel(Config c, int pass, const uint32_t* kin, const uint32_t* vin,
                                                          uint32_t* kout, uint32_t* vout) {
   __shared__ ScatterLds L;
   static_assert(sizeof(ScatterLds) <= 160 * 1024 / kScatterPerCu, "workgroups per CU");
   static_assert(kSortBins == 2 * kBlock, "two digits per thread");
   WsHeader* h = c.hdr;
   const uint32_t nsc = h->schunks, K = h->kept;
+  if (FOLD) {  // a workgroup per chunk: its entries load with the counts (in bounds: the grid is schunk_max)
+    const uint32_t k = blockIdx.x;
+    const uint4 ch = c.schunk[k];
+    const uint2 fc = c.schunk_frame[k];
+    asm volatile("" ::"s"(ch.x), "s"(ch.y), "s"(fc.x));  // keeps the loads above the check
+    if (k >= nsc) return;  // uniform
+    if (ch.y - ch.x <= (uint32_t)kSortTile / 2u)  // uniform
+      scatter_chunk<kSortItems / 2, ROWS, true>(c, L, pass, k, ch, fc, K, kin, vin, kout, vout);
+    else
+      scatter_chunk<kSortItems, ROWS, true>(c, L, pass, k, ch, fc, K, kin, vin, kout, vout);
+    return;
+  }
   // chunks dealt to the XCDs in contiguous blocks: a frame's chunks share
   // one L2, where their neighbouring digit runs merge into whole lines and
   // their count rows are read once; a grid of resident size walks them
@@ -692,9 +787,9 @@ __global__ __launch_bounds__(kBlock, kScatterPerCu) void scatter_kernel(Config c
     const uint2 fc = c.schunk_frame[k];
     // a chunk of at most half a tile: half the rounds per wave
     if (ch.y - ch.x <= (uint32_t)kSortTile / 2u)  // uniform
-      scatter_chunk<kSortItems / 2>(c, L, pass, k, ch, fc, K, kin, vin, kout, vout);
+      scatter_chunk<kSortItems / 2, ROWS, false>(c, L, pass, k, ch, fc, K, kin, vin, kout, vout);
     else
-      scatter_chunk<kSortItems>(c, L, pass, k, ch, fc, K, kin, vin, kout, vout);
+      scatter_chunk<kSortItems, ROWS, false>(c, L, pass, k, ch, fc, K, kin, vin, kout, vout);
   }
 }
 
@@ -726,13 +821,19 @@ hipError_t launch_compact(const Config& c, uint32_t* kout, hipStream_t st) {
 
 hipError_t launch_radix_pass(const Config& c, int pass, const uint32_t* kin, const uint32_t* vin, uint32_t* kout,
                              uint32_t* vout, hipStream_t st) {
+  if (c.fold_rows) {  // counted by the launch before
+    hipLaunchKernelGGL((scatter_kernel<kSmallRows, 2, true>), dim3((uint32_t)c.schunk_max), dim3(kBlock), 0, st, c, pass, kin,
+                       vin, kout, vout);
+    return hipGetLastError();
+  }
   // grids of resident size (idle workgroups still cost dispatch time)
   const uint32_t cgrid = min((uint32_t)c.schunk_max, (uint32_t)kCountGrid);
   hipLaunchKernelGGL(count_kernel, dim3(cgrid), dim3(kBlock), 0, st, c, pass, kin);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const uint32_t sgrid = min((c.schunk_max + 7u) / 8u * 8u, (uint32_t)(kScatterPerCu * kCus));  // whole rounds of the XCDs
-  hipLaunchKernelGGL(scatter_kernel, dim3(sgrid), dim3(kBlock), 0, st, c, pass, kin, vin, kout, vout);
+  hipLaunchKernelGGL((scatter_kernel<8, kScatterPerCu, false>), dim3(sgrid), dim3(kBlock), 0, st, c, pass, kin, vin, kout,
+                     vout);
   return hipGetLastError();
 }
 
