@@ -70,6 +70,7 @@ struct Plan {
   int32_t B, S, C, M, cap, max_rois, W;
   int32_t cell_shift, ncx, ncy, ncells;
   int32_t kb, passes, dbits;
+  int32_t fold_rows, frame_chunks;
   int64_t fchunk_points, fchunk_max, filter_grid, schunk_max, vtile_max, mean_grid;
   size_t off_hdr, off_cellmask, off_cellany, off_budgetmask, off_fchunk_first, off_fbits, off_fcount, off_fchunk_lo, off_fchunk_frame, off_wgframe, off_spare, off_fprefix,
       off_fstart, off_schunk_first, off_schunk, off_schunk_frame, off_cnt, off_vtile, off_vt_first, off_hcount, off_hpre, off_mtile, off_trow, off_keys[2], off_vals[2], off_rec,
@@ -134,7 +135,24 @@ mmbev_status_t make_plan(const mmbev_grid_t* g, int64_t N, int32_t max_rois, int
     p->fchunk_max = (N + P - 1) / P + (int64_t)kWaves * p->B;  // each frame rounded up to whole workgroups
     p->filter_grid = std::max<int64_t>(1, (p->fchunk_max + kWaves - 1) / kWaves);
   }
-  p->schunk_max = std::min<int64_t>(N / (kSortTile / 2) + p->B, (int64_t)kMaxFrameChunks * p->B) + 1;  // half-tile chunks too
+  // small calls of a few frames count each radix pass's digits where its
+  // pairs are written: rows for every chunk a frame can have, as long as they
+  // fit the space of hpos and hplace (from about 2,000 points on).  With room
+  // for twice the rows a frame may have twice the chunks: a frame of 250,000
+  // pairs has one tile to a workgroup then instead of two, and twice as many
+  // compute units at work (its three scatter launches 53.7 -> 51.9 us; its
+  // workgroups sum twice the rows).
+  p->fold_rows = 0;
+  p->frame_chunks = kMaxFrameChunks;
+  if (p->fchunk_max <= kSmallChunks && p->B <= kFoldFrames)
+    for (const int32_t most : {kFoldFrameChunks, kMaxFrameChunks}) {
+      const int64_t rows = std::min<int64_t>(most, N / (kSortTile / 2) + 1);
+      if ((int64_t)p->passes * p->B * rows * kSortBins > 2 * N) continue;
+      p->fold_rows = (int32_t)rows;
+      p->frame_chunks = most;
+      break;
+    }
+  p->schunk_max = std::min<int64_t>(N / (kSortTile / 2) + p->B, (int64_t)p->frame_chunks * p->B) + 1;  // half-tile chunks too
   p->vtile_max = N / kVoxTile + p->B + 1;
   p->mean_grid = std::min<int64_t>((n1 + kMeanTile - 1) / kMeanTile, 2048);  // measured best (1536 and 4096 slower)
   size_t o = 0;
@@ -377,16 +395,9 @@ mmbev_status_t voxelize(const mmbev_points_t* points, const uint8_t* sweep_ids, 
   const int32_t lds_words = c.lds_wmask >= 0 ? c.lds_wmask + p.ncells * p.W : c.lds_cell + c.lds_cell_cap;
   c.lds_dyn_bytes = (int32_t)(((size_t)lds_words * 4 + 15) / 16 * 16);
   c.small_call = p.fchunk_max <= kSmallChunks;
-  // small calls of a few frames count each radix pass's digits where its
-  // pairs are written: rows for every chunk a frame can have (half tiles, at
-  // most kMaxFrameChunks), as long as they fit the space of hpos and hplace
-  // (from about 2,000 points on)
-  {
-    const int64_t rows = std::min<int64_t>(kMaxFrameChunks, N / (kSortTile / 2) + 1);
-    const bool fold = c.small_call && p.B <= kFoldFrames && (int64_t)p.passes * p.B * rows * kSortBins <= 2 * N;
-    c.fold_rows = fold ? (int32_t)rows : 0;
-    c.fold_cnt = c.hpos;
-  }
+  c.fold_rows = p.fold_rows;
+  c.fold_cnt = c.hpos;
+  c.frame_chunks = p.frame_chunks;
   c.schunk_max = (int32_t)p.schunk_max;
   c.vtile_max = (int32_t)p.vtile_max;
   c.mean_grid = (int32_t)p.mean_grid;

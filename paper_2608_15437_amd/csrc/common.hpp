@@ -41,6 +41,7 @@ constexpr int kSortTile = kBlock * kSortItems;  // 2048 pairs
 constexpr int kCountItems = 16;       // pairs per thread per batch of the count kernel
 constexpr int kHalfTileFramePairs = 16 * kSortTile / 2;  // frames of at most this many pairs may take half-tile chunks
 constexpr int kMaxFrameChunks = 64;   // pair chunks of one frame at most (chunks never straddle frames)
+constexpr int kFoldFrameChunks = 128;  // ... in calls whose radix passes have no count launch, if their rows fit
 constexpr int kScanItems = 16;        // items per thread in the single-workgroup scans
 constexpr int kScanTile = kBlock * kScanItems;  // 4096
 constexpr int kMeanTile = kBlock;     // one voxel per thread
@@ -174,7 +175,8 @@ struct Config {
   // "not staged"
   int32_t lds_pose_cap, lds_roi_cap, lds_bm_cap, lds_cell_cap, lds_roi, lds_bm, lds_cell, lds_dyn_bytes;
   int32_t lds_wmask;       // the filter's own per-cell ROI words (several words per cell), word offset; -1: none
-  int32_t schunk_max;      // bound on pair chunks: min(N / (kSortTile / 2) + B, kMaxFrameChunks * B) + 1
+  int32_t frame_chunks;    // pair chunks of one frame at most
+  int32_t schunk_max;      // bound on pair chunks: min(N / (kSortTile / 2) + B, frame_chunks * B) + 1
   int32_t vtile_max;       // bound on voxel tiles: N / kVoxTile + B + 1
   int32_t mean_grid;
 };
@@ -299,15 +301,16 @@ __device__ __forceinline__ int32_t frame_of_chunk(const uint32_t* first, int32_t
   return lo;
 }
 
-// Pairs per chunk of a frame of n kept pairs: at most kMaxFrameChunks
+// Pairs per chunk of a frame of n kept pairs: at most max_chunks
 // chunks, each a whole number of scatter tiles, at least min_tiles of them;
 // half tiles (the scatter ranks a chunk of at most half a tile four rounds
 // per wave instead of eight) for a frame of at most kHalfTileFramePairs
 // pairs when the call allows them (half: its half-tile chunks fit one round
 // of the scatter's resident workgroups).
-__device__ __forceinline__ uint32_t frame_chunk_pairs(uint32_t n, uint32_t min_tiles, bool half) {
+__device__ __forceinline__ uint32_t frame_chunk_pairs(uint32_t n, uint32_t min_tiles, bool half,
+                                                      uint32_t max_chunks) {
   if (half && n <= (uint32_t)kHalfTileFramePairs) return (uint32_t)kSortTile / 2u;
-  uint32_t ch = (n + kMaxFrameChunks - 1) / kMaxFrameChunks;
+  uint32_t ch = (n + max_chunks - 1) / max_chunks;
   ch = (ch + kSortTile - 1) / kSortTile * kSortTile;
   return max(ch, min_tiles * (uint32_t)kSortTile);
 }

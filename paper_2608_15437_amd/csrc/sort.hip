@@ -13,7 +13,7 @@
 //
 // segments -- one workgroup: the kept-pair prefix of the filter chunks, the
 //             first pair of every frame (the prefix at its first filter
-//             chunk), and the pair chunks (at most kMaxFrameChunks per frame,
+//             chunk), and the pair chunks (at most frame_chunks per frame,
 //             whole scatter tiles, or half tiles for frames of at most
 //             kHalfTileFramePairs pairs when the call allows; the last of a
 //             frame shorter) and the voxel tiles of the later kernels
@@ -182,13 +182,13 @@ __device__ __forceinline__ void segments_body(const Config& c, uint32_t* s_tmp, 
   __syncthreads();
   if (lds)
     for (int g = tid; g <= c.B; g += BLOCK) c.fstart[g] = s_fstart[g];
-  // pair chunks (at most kMaxFrameChunks per frame, of frame_chunk_pairs
+  // pair chunks (at most frame_chunks per frame, of frame_chunk_pairs
   // pairs: whole kSortTile multiples, the last one of a frame shorter) and
   // voxel tiles (kVoxTile sorted pairs, the last one of a frame shorter):
   // the frames' counts scanned into their first indices, then every chunk
   // and tile written by its own thread (its frame found by a search over
   // the first indices: the last frame whose first index is at most its own)
-  const uint32_t mt = chunk_min_tiles(K, c.B);
+  const uint32_t mt = chunk_min_tiles(K, c.B), mc = (uint32_t)c.frame_chunks;
   const bool half = half_tile_chunks(K, c.B);
   const int per = (c.B + BLOCK - 1) / BLOCK;
   const int b0 = tid * per;
@@ -198,7 +198,7 @@ __device__ __forceinline__ void segments_body(const Config& c, uint32_t* s_tmp, 
     const int b = b0 + j;
     if (b < c.B) {
       const uint32_t n = fstart[b + 1] - fstart[b];
-      mine += (n + frame_chunk_pairs(n, mt, half) - 1) / frame_chunk_pairs(n, mt, half);
+      mine += (n + frame_chunk_pairs(n, mt, half, mc) - 1) / frame_chunk_pairs(n, mt, half, mc);
       most = max(most, (unsigned long long)n << 32 | (uint32_t)~(uint32_t)b);
       mine_vt += (n + kVoxTile - 1) / kVoxTile;
     }
@@ -223,7 +223,7 @@ __device__ __forceinline__ void segments_body(const Config& c, uint32_t* s_tmp, 
       const uint32_t n = fstart[b + 1] - fstart[b];
       sfirst[b] = min(run, cap);
       tfirst[b] = min(run_vt, cap_vt);
-      run += (n + frame_chunk_pairs(n, mt, half) - 1) / frame_chunk_pairs(n, mt, half);
+      run += (n + frame_chunk_pairs(n, mt, half, mc) - 1) / frame_chunk_pairs(n, mt, half, mc);
       run_vt += (n + kVoxTile - 1) / kVoxTile;
     }
   }
@@ -243,7 +243,7 @@ __device__ __forceinline__ void segments_body(const Config& c, uint32_t* s_tmp, 
   for (uint32_t k = tid; k < nsc; k += BLOCK) {
     const int32_t b = frame_of(sfirst, k);
     const uint32_t f0 = fstart[b], f1 = fstart[b + 1];
-    const uint32_t CH = frame_chunk_pairs(f1 - f0, mt, half);
+    const uint32_t CH = frame_chunk_pairs(f1 - f0, mt, half, mc);
     const uint32_t k0 = sfirst[b], k1 = sfirst[b + 1];
     const uint32_t lo = f0 + (k - k0) * CH;
     c.schunk[k] = make_uint4(lo, min(lo + CH, f1), (uint32_t)b, f0);
@@ -461,7 +461,8 @@ __global__ __launch_bounds__(kCompactBlock) void compact_kernel(Config c, uint32
     dst = t.x;
     fs = t.y;
     fe = t.z;
-    if (c.fold_rows) chunk_pairs = frame_chunk_pairs(fe - fs, chunk_min_tiles(t.w, c.B), half_tile_chunks(t.w, c.B));
+    if (c.fold_rows)
+      chunk_pairs = frame_chunk_pairs(fe - fs, chunk_min_tiles(t.w, c.B), half_tile_chunks(t.w, c.B), (uint32_t)c.frame_chunks);
   }
 #pragma unroll
   for (int u = 0; u < kPoseRegs; ++u)
@@ -577,7 +578,7 @@ __device__ __forceinline__ void scatter_chunk(const Config& c, ScatterLds& L, in
   uint32_t key[kSortItems], val[kSortItems], nkey[kSortItems], nval[kSortItems];
   if (lo < hi) load_sort_tile<NR>(kin, vin, lo, hi, key, val);
   // the first ROWS count rows of the frame's chunks (at most
-  // kMaxFrameChunks rows) go out now and are summed after the first
+  // frame_chunks rows) go out now and are summed after the first
   // tile is ranked: digit bases = frame start + the frame's smaller
   // digits + this digit in the frame's earlier chunks
   // (FOLD: row j of the frame's own rows is its chunk j, else row k chunk k)
