@@ -310,7 +310,7 @@ __device__ __forceinline__ int32_t frame_of_chunk(const uint32_t* first, int32_t
 __device__ __forceinline__ uint32_t frame_chunk_pairs(uint32_t n, uint32_t min_tiles, bool half,
                                                       uint32_t max_chunks) {
   if (half && n <= (uint32_t)kHalfTileFramePairs) return (uint32_t)kSortTile / 2u;
-  uint32_t ch = (n + max_chunks - 1) / max_chunks;
+  uint32_t ch = (n + max_chunks - 1) >> __builtin_ctz(max_chunks);  // a power of two
   ch = (ch + kSortTile - 1) / kSortTile * kSortTile;
   return max(ch, min_tiles * (uint32_t)kSortTile);
 }

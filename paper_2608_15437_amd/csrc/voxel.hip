@@ -232,20 +232,20 @@ __device__ void cap_frame(const Config& c, int32_t b, CapLds& S, uint32_t t0, ui
   // tests that afterwards, so that its loads are in flight together)
   const uint32_t nw = (nk + 31) / 32;
   // 1. the first places: marked here in LDS when the bitmap fits there
-  // (every workgroup of a shared cap for itself: LDS atomics, 32 slots of a
-  // thread in flight), else by the heads kernel in the workspace (the
+  // (every workgroup of a shared cap for itself, with LDS atomics), else by the heads kernel in the workspace (the
   // compaction cleared it)
   const uint32_t* gbits = c.capbits + wbase;
   constexpr int kUnroll = 32;  // loads in flight per thread: one workgroup walks the whole frame
   if (kLds) {
     for (uint32_t w = tid; w < nw; w += kFinBlock) S.area[w] = 0u;
     __syncthreads();  // the tiles' counts are in place, the bits cleared
-    for (uint32_t base = tid; base < nk; base += kFinBlock * kUnroll) {
-      uint32_t p[kUnroll];
+    constexpr int kMarks = 16;  // slots of a thread in flight
+    for (uint32_t base = tid; base < nk; base += kFinBlock * kMarks) {
+      uint32_t p[kMarks];
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) p[u] = c.hplace[fs + min(base + u * kFinBlock, nk - 1u)];
+      for (int u = 0; u < kMarks; ++u) p[u] = c.hplace[fs + min(base + u * kFinBlock, nk - 1u)];
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
+      for (int u = 0; u < kMarks; ++u) {
         const uint32_t i = base + u * kFinBlock;
         if (i < nk && i % kVoxTile < hc[i / kVoxTile]) {
           const uint32_t q = min(p[u] - fs, nk - 1u);
@@ -293,13 +293,18 @@ __device__ void cap_frame(const Config& c, int32_t b, CapLds& S, uint32_t t0, ui
   static_assert(kCapStepSlots == (uint32_t)kFinBlock * kUnroll, "one step of the flag pass");
   for (uint32_t step = g; step * kCapStepSlots < nk; step += G) {  // uniform: every wave takes every step
     const uint32_t base = step * kCapStepSlots + (uint32_t)(tid & ~63);
-    uint32_t p[kUnroll], n[kUnroll];
+    // the slots' places in flight together, and their tiles' counts: row u's
+    // slots lie in one tile for the whole step (kVoxTile / kFinBlock rows to a
+    // tile), one count per tile
+    constexpr int kRowsPerTile = kVoxTile / kFinBlock;
+    static_assert(kVoxTile % kFinBlock == 0 && kCapStepSlots % kVoxTile == 0, "a row lies in one tile");
+    uint32_t p[kUnroll], n[kUnroll / kRowsPerTile];
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {  // clamped, unconditional loads
-      const uint32_t i = min(base + u * kFinBlock + (uint32_t)lane, nk - 1u);
-      p[u] = c.hplace[fs + i];
-      n[u] = hc[i / kVoxTile];
-    }
+    for (int u = 0; u < kUnroll; ++u)  // clamped, unconditional loads
+      p[u] = c.hplace[fs + min(base + u * kFinBlock + (uint32_t)lane, nk - 1u)];
+#pragma unroll
+    for (int u = 0; u < kUnroll / kRowsPerTile; ++u)
+      n[u] = hc[min(step * kCapStepSlots + u * kVoxTile, nk - 1u) / kVoxTile];
     // the wave's flag words of this step: ballot u's low half goes to lane
     // u, its high half to lane 32 + u, and every lane stores one word
     static_assert(kUnroll == 32, "one flag word per lane and step");
@@ -307,7 +312,7 @@ __device__ void cap_frame(const Config& c, int32_t b, CapLds& S, uint32_t t0, ui
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       const uint32_t i = base + u * kFinBlock + (uint32_t)lane;
-      const uint64_t m = __ballot(i < nk && (i % kVoxTile) < n[u] && p[u] <= thr);
+      const uint64_t m = __ballot(i < nk && (i % kVoxTile) < n[u / kRowsPerTile] && p[u] <= thr);
       if ((lane & 31) == u) wv = lane < 32 ? (uint32_t)m : (uint32_t)(m >> 32);
     }
     const uint32_t i0 = base + (uint32_t)(lane & 31) * kFinBlock;  // the slots of this lane's word
@@ -542,11 +547,22 @@ __global__ __launch_bounds__(kBlock, PER_CU) void mean_kernel(Config c, const ui
     double sum[8];
 #pragma unroll
     for (int f = 0; f < 8; ++f) sum[f] = 0.0;
-    for (uint32_t m0 = 0; m0 < cnt; m0 += BATCH) {
-      uint32_t q[BATCH];
+    auto places = [&](uint32_t m0, uint32_t* q) {
 #pragma unroll
       for (int u = 0; u < BATCH; ++u)
         q[u] = min(m0 + u == 0 ? q0 : vals[min(s0 + (BATCH > 2 ? min(m0 + u, cnt - 1u) : m0 + u), K - 1u)], K - 1u);
+    };
+    uint32_t qn[BATCH];  // small calls: the next batch's places, loaded with this batch's records
+    if (BATCH > 2 && cnt > 0u) places(0u, qn);
+    for (uint32_t m0 = 0; m0 < cnt; m0 += BATCH) {
+      uint32_t q[BATCH];
+      if (BATCH > 2) {
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) q[u] = qn[u];
+        places(m0 + BATCH, qn);  // past the last point: its place again
+      } else {
+        places(m0, q);
+      }
       uint32_t w[BATCH][RW];
 #pragma unroll
       for (int u = 0; u < BATCH; ++u) {  // 16-byte loads when RW is a multiple of four, else 8-byte loads
