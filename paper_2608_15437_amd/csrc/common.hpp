@@ -54,16 +54,6 @@ constexpr int kCountGrid = 2048;     // count workgroups (eight per CU)
 constexpr int kMaxCapSteps = 48;             // steps of a cap shared by several workgroups (frames of up to 1.5M pairs)
 constexpr uint32_t kCapStepSlots = 1u << 15;  // slots of one step of a cap's flag pass
 
-constexpr int kCapLdsWords = 16384;          // a capped frame's first-place bits in LDS up to this many words
-
-// Whether the first-place bits of a frame of n pairs fit the cap
-// workgroups' LDS, and otherwise (and only if the frame can exceed the cap)
-// are kept in the workspace: cleared by the compaction, set by the heads
-// kernel.  (Setting them there costs an atomic per voxel also in frames that
-// turn out to stay within the cap: 9 us for a frame of 250,000 pairs.)
-__device__ __forceinline__ bool cap_bits_in_lds(uint32_t n) { return (n + 31u) / 32u <= (uint32_t)kCapLdsWords; }
-__device__ __forceinline__ bool cap_bits_global(uint32_t n, int32_t cap) { return n > (uint32_t)cap && !cap_bits_in_lds(n); }
-
 struct alignas(256) WsHeader {
   int32_t fault;              // byte 0: MMBEV_FAULT_* bits of the last call
   uint32_t epoch;             // call counter

@@ -468,7 +468,7 @@ __global__ __launch_bounds__(kCompactBlock) void compact_kernel(Config c, uint32
   for (int u = 0; u < kPoseRegs; ++u)
     if (tid + u * kCompactBlock < np) s_pose[tid + u * kCompactBlock] = pv[u];
   for (int e = tid + kPoseRegs * kCompactBlock; e < np; e += kCompactBlock) s_pose[e] = c.poses[(int64_t)b * np + e];
-  if (cap_bits_global(fe - fs, c.cap)) {  // uniform: the frame's first-place bits over this chunk's places cleared
+  if (fe - fs > (uint32_t)c.cap) {  // uniform: the frame may exceed the cap: its first-place bits over this chunk's places cleared
     uint32_t* bits = c.capbits + fs / 32 + (uint32_t)b;  // the heads kernel sets them
     for (uint32_t w = (dst - fs) / 32 + tid; w < (dst - fs + cnt + 31) / 32; w += kCompactBlock) bits[w] = 0u;
   }

@@ -79,7 +79,7 @@ __global__ __launch_bounds__(kBlock) void heads_kernel(Config c, const uint32_t*
         c.hpos[slot] = lo + j * kBlock + tid;
         c.hplace[slot] = val[j];
       }
-    if (cap_bits_global(fe - ff, c.cap)) {  // uniform: the heads' places marked for the cap (bits cleared by the compaction)
+    if (fe - ff > (uint32_t)c.cap) {  // uniform: the heads' places marked for the cap (bits cleared by the compaction)
       uint32_t* bits = c.capbits + ff / 32 + fb;
 #pragma unroll
       for (int j = 0; j < kHeadItems; ++j)
@@ -95,7 +95,8 @@ __global__ __launch_bounds__(kBlock) void heads_kernel(Config c, const uint32_t*
 
 constexpr int kFinBlock = 1024;
 constexpr int kFinWaves = kFinBlock / 64;
-constexpr int kCapLdsTiles = kCapLdsWords * 32 / kVoxTile + 1;  // tiles of a frame whose bits fit LDS, at most
+constexpr int kCapLdsWords = 16384;  // bitmaps of a capped frame in LDS up to this many words
+constexpr int kCapLdsTiles = 8192;   // voxel counts of a capped frame's tiles in LDS up to this many tiles
 
 // Exclusive prefix of n values in[0..n) written to out by one workgroup of
 // kFinBlock threads; returns the total.
@@ -175,7 +176,7 @@ __device__ void finalize_offsets(const Config& c, uint32_t* s_tmp) {
 
 struct CapLds {
   uint32_t hc[kCapLdsTiles];    // voxels of the frame's tiles
-  uint32_t area[kCapLdsWords];  // the first-place bits, then kept flags
+  uint32_t area[kCapLdsWords];  // the first-place bits (copied from the workspace), then kept flags and their word prefix
   uint32_t tmp[kFinWaves];
   uint32_t sel;
 };
@@ -205,8 +206,8 @@ __device__ __forceinline__ uint32_t cap_share(uint32_t nk) {
 // [fstart[b], fstart[b+1]) in order (tile after tile; slot lo + j of a tile
 // holds its voxel j when j < its voxel count): slot order restricted to the
 // voxels is key order.  The first places are marked in a bitmap over the
-// frame's places (here in LDS; for frames whose bitmap does not fit there by the
-// heads kernel in the workspace), the max_voxels-th marked place is found from a prefix of
+// frame's places (by the heads kernel, every tile's heads at once; the
+// compaction clears the frame's words), the max_voxels-th marked place is found from a prefix of
 // the words' popcounts, the kept voxels are flagged in slot order (one
 // ballot per 64 slots) and numbered by a prefix of those flag words.  The
 // tables sit in LDS when they fit, otherwise in the frame's regions of the
@@ -231,30 +232,20 @@ __device__ void cap_frame(const Config& c, int32_t b, CapLds& S, uint32_t t0, ui
   // tile's count (every pass loads at clamped slots, unconditionally, and
   // tests that afterwards, so that its loads are in flight together)
   const uint32_t nw = (nk + 31) / 32;
-  // 1. the first places: marked here in LDS when the bitmap fits there
-  // (every workgroup of a shared cap for itself, with LDS atomics), else by the heads kernel in the workspace (the
-  // compaction cleared it)
+  // 1. the first places, marked in the workspace by the heads kernel (the
+  // compaction cleared them); copied to LDS when the tables fit there
   const uint32_t* gbits = c.capbits + wbase;
-  constexpr int kUnroll = 32;  // loads in flight per thread: one workgroup walks the whole frame
-  if (kLds) {
-    for (uint32_t w = tid; w < nw; w += kFinBlock) S.area[w] = 0u;
-    __syncthreads();  // the tiles' counts are in place, the bits cleared
-    constexpr int kMarks = 16;  // slots of a thread in flight
-    for (uint32_t base = tid; base < nk; base += kFinBlock * kMarks) {
-      uint32_t p[kMarks];
+  if (kLds)
+    for (uint32_t base = 0; base < nw; base += kFinBlock * 8) {
+      uint32_t v[8];
 #pragma unroll
-      for (int u = 0; u < kMarks; ++u) p[u] = c.hplace[fs + min(base + u * kFinBlock, nk - 1u)];
+      for (int u = 0; u < 8; ++u) v[u] = gbits[min(base + u * kFinBlock + (uint32_t)tid, nw - 1u)];  // in flight together
 #pragma unroll
-      for (int u = 0; u < kMarks; ++u) {
-        const uint32_t i = base + u * kFinBlock;
-        if (i < nk && i % kVoxTile < hc[i / kVoxTile]) {
-          const uint32_t q = min(p[u] - fs, nk - 1u);
-          atomicOr(&S.area[q >> 5], 1u << (q & 31u));
-        }
-      }
+      for (int u = 0; u < 8; ++u)
+        if (base + u * kFinBlock + tid < nw) S.area[base + u * kFinBlock + tid] = v[u];
     }
-  }
   const uint32_t* bits = kLds ? S.area : gbits;
+  constexpr int kUnroll = 32;  // loads in flight per thread: one workgroup walks the whole frame
   __syncthreads();  // the tiles' counts and the bits are in place
   // 2. the max_voxels-th smallest first place: thread t counts a contiguous run of words
   {
@@ -389,7 +380,7 @@ __global__ __launch_bounds__(kFinBlock) void fincap_kernel(Config c) {
   // the frame's voxels (and, for tables in the workspace, its tiles' counts)
   const size_t words = (size_t)c.N / 32 + (size_t)c.B + 1;
   const uint32_t fs = c.fstart[b], nk = max(c.fstart[b + 1], fs) - fs;
-  const bool lds = cap_bits_in_lds(nk);  // and then its tiles' counts too
+  const bool lds = nt <= (uint32_t)kCapLdsTiles && 2 * ((nk + 31) / 32) <= (uint32_t)kCapLdsWords;
   const uint32_t g = helper ? (uint32_t)blockIdx.x - (uint32_t)c.B : 0u;
   if (g >= cap_share(nk) || (helper && nk <= (uint32_t)c.cap)) return;  // uniform: a helper with no work
   uint32_t mine = 0;

@@ -1,8 +1,8 @@
 """Parity with the oracle at the edges of the small-call paths: radix passes
 without count launches (from about 2,000 points, up to eight frames and 2,048
 filter chunks), chunk sizes of one, two and three tiles and of half a tile,
-one to four passes, and frames over the cap on both sides of the largest whose
-first places are marked in LDS (524,288 pairs).  Structure bit for bit."""
+one to four passes, and frames over the cap of 16 and 17 steps of its flag
+pass.  Structure bit for bit."""
 import numpy as np
 import pytest
 
@@ -45,6 +45,6 @@ def test_fold_edges(gpu_lib, sizes, dims, cap):
 
 
 @pytest.mark.parametrize("n", [524_288, 524_289])
-def test_cap_bitmap_edge(gpu_lib, n):
+def test_cap_steps_edge(gpu_lib, n):
     vz, exp = check(gpu_lib, _uniform([n, 70_000], (256, 256, 16), 150_000), label=f"cap {n}")
     assert vz.header()["capped_voxels"] > 150_000 and int(exp["voxel_offsets"][1]) == 150_000
