@@ -152,7 +152,15 @@ mmbev_status_t make_plan(const mmbev_grid_t* g, int64_t N, int32_t max_rois, int
       p->frame_chunks = most;
       break;
     }
-  p->schunk_max = std::min<int64_t>(N / (kSortTile / 2) + p->B, (int64_t)p->frame_chunks * p->B) + 1;  // half-tile chunks too
+  // half-tile chunks too.  The workspace holds kMaxFrameChunks chunks a frame
+  // whatever the call's own limit is, so that its size grows with N across
+  // the edges of the folded calls: a buffer sized for a stream's largest call
+  // takes the smaller ones
+  const auto chunks = [&](int32_t most) {
+    return std::min<int64_t>(N / (kSortTile / 2) + p->B, (int64_t)most * p->B) + 1;
+  };
+  const int64_t sized_chunks = chunks(kMaxFrameChunks);
+  p->schunk_max = chunks(p->frame_chunks);
   p->vtile_max = N / kVoxTile + p->B + 1;
   p->mean_grid = std::min<int64_t>((n1 + kMeanTile - 1) / kMeanTile, 2048);  // measured best (1536 and 4096 slower)
   size_t o = 0;
@@ -175,9 +183,14 @@ mmbev_status_t make_plan(const mmbev_grid_t* g, int64_t N, int32_t max_rois, int
   p->off_fprefix = take((size_t)(p->fchunk_max + 1) * 4);
   p->off_fstart = take((size_t)(p->B + 1) * 4);
   p->off_schunk_first = take((size_t)(p->B + 1) * 4);
-  p->off_schunk = take((size_t)p->schunk_max * 16);
-  p->off_schunk_frame = take((size_t)p->schunk_max * 8);
-  p->off_cnt = take((size_t)p->schunk_max * kSortBins * 4);
+  p->off_schunk = take((size_t)sized_chunks * 16);
+  p->off_schunk_frame = take((size_t)sized_chunks * 8);
+  p->off_cnt = take((size_t)sized_chunks * kSortBins * 4);
+  if (p->schunk_max > sized_chunks) {  // the longer tables of a folded call lie over the count rows, which it has no use for
+    static_assert(kFoldFrameChunks <= 2 * kMaxFrameChunks && 2 * (16 + 8) + 256 <= kSortBins * 4, "they fit: two entries to a count row, and the padding");
+    p->off_schunk = p->off_cnt;
+    p->off_schunk_frame = p->off_cnt + align256((size_t)p->schunk_max * 16);
+  }
   p->off_vtile = take((size_t)p->vtile_max * 16);
   p->off_vt_first = take((size_t)(p->B + 1) * 4);
   p->off_hcount = take((size_t)p->vtile_max * 4);

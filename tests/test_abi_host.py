@@ -101,6 +101,23 @@ def test_workspace_bytes_validation(mb):
     assert mb.roi_voxelize_workspace_bytes(g, 347200, 8, 32) > mb.roi_voxelize_workspace_bytes(g, 347200, 3, 32)
 
 
+@pytest.mark.parametrize("frames", [1, 2, 3, 4, 5, 8, 9])
+@pytest.mark.parametrize("dims", [(64, 64, 8), (1440, 1440, 40), (2160, 2160, 40)])
+def test_workspace_grows_with_the_points(mb, frames, dims):
+    """A buffer sized for the largest call of a stream takes its smaller calls, across the sizes where the chunks of the
+    radix passes change: few points, one tile to a chunk, and the last small call (2,048 filter chunks of 256 points, the
+    frames' partial workgroups among them)."""
+    g = mb.grid_params((-54, -54, -5), (0.075, 0.075, 0.2), dims, 10, 120000, 10, frames)
+    last = 256 * (2048 - 4 * frames)
+    assert 515_000 < last < 524_288
+    sizes = sorted({n + d for n in [1, 768, 1024, 1536, 2048, 2304, 20_000, 65_536 * frames, 98_304 * frames,
+                                    196_608 * frames, 393_216, last, 524_288, 1_048_576]
+                    for d in (-2049, -1024, -257, -1, 0, 1, 255, 256, 257, 1025, 5000) if n + d > 0})
+    need = [mb.roi_voxelize_workspace_bytes(g, n, 5, 32) for n in sizes]
+    shrinks = [(a, b, p - q) for a, b, p, q in zip(sizes, sizes[1:], need, need[1:]) if q < p]
+    assert not shrinks, f"(points, more points, bytes fewer): {shrinks}"
+
+
 def test_voxelize_rejects_bad_arguments_before_any_launch(mb):
     L = mb.load()
     g = mb.grid_params((-4, -4, -1), (0.5, 0.5, 0.5), (16, 16, 4), 2, 3, 2, 1)
