@@ -340,7 +340,6 @@ mmbev_status_t voxelize(const mmbev_points_t* points, const uint8_t* sweep_ids, 
   c.ncx = p.ncx;
   c.ncy = p.ncy;
   c.ncells = p.ncells;
-  c.kb = p.kb;
   c.passes = p.passes;
   c.dbits = p.dbits;
   c.vec = (((uintptr_t)points->feat & 15) == 0 && (points->stride & 3) == 0 && ((uintptr_t)sweep_ids & 3) == 0) ? 1
@@ -367,7 +366,7 @@ mmbev_status_t voxelize(const mmbev_points_t* points, const uint8_t* sweep_ids, 
   c.schunk_first = (uint32_t*)(ws + p.off_schunk_first);
   c.schunk = (uint4*)(ws + p.off_schunk);
   c.schunk_frame = (uint2*)(ws + p.off_schunk_frame);
-  c.cnt = (uint32_t*)(ws + p.off_cnt);
+  c.cnt = (uint32_t*)(ws + (p.fold_rows ? p.off_hpos : p.off_cnt));
   c.vtile = (uint4*)(ws + p.off_vtile);
   c.vt_first = (uint32_t*)(ws + p.off_vt_first);
   c.hcount = (uint32_t*)(ws + p.off_hcount);
@@ -409,7 +408,6 @@ mmbev_status_t voxelize(const mmbev_points_t* points, const uint8_t* sweep_ids, 
   c.lds_dyn_bytes = (int32_t)(((size_t)lds_words * 4 + 15) / 16 * 16);
   c.small_call = p.fchunk_max <= kSmallChunks;
   c.fold_rows = p.fold_rows;
-  c.fold_cnt = c.hpos;
   c.frame_chunks = p.frame_chunks;
   c.schunk_max = (int32_t)p.schunk_max;
   c.vtile_max = (int32_t)p.vtile_max;

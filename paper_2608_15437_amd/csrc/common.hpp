@@ -90,12 +90,15 @@ struct Config {
   int32_t cell_pad;        // voxels added around each ROI's cell rectangle
   uint32_t Dx, Dy, Dz;
   int32_t cell_shift, ncx, ncy, ncells;
-  // keys: (iz*Dy + iy)*Dx + ix < 2^kb, sorted within each frame in `passes`
+  // (the order and widths keep these where the kernels load them in one go:
+  // three words in a row that a kernel reads become a load of four)
+  int32_t frame_chunks;  // pair chunks of one frame at most
+  // keys: (iz*Dy + iy)*Dx + ix, sorted within each frame in `passes`
   // least-significant-digit passes of dbits bits
-  int32_t kb, passes, dbits;
-  int32_t vec;  // 16-byte vector loads allowed
-  int32_t fuse_stage;  // the point filter lays out the call and builds its frame's tables (no staging kernel)
-  int32_t fold_rows;   // rows per frame of fold_cnt; 0: every radix pass has a count launch of its own
+  int32_t passes, dbits;
+  int16_t vec;         // 16-byte vector loads allowed
+  int16_t fuse_stage;  // the point filter lays out the call and builds its frame's tables (no staging kernel)
+  int32_t fold_rows;   // calls whose radix passes have no count launch: count rows per frame and pass; 0: every pass has one
   int32_t small_call;  // at most kSmallChunks filter chunks: the compaction launch does the segments kernel's work
   // out-of-ROI keep (Alg. 1 rate rho_out): threshold round(rho_out * 2^24)
   // on the top 24 bits of the point's SplitMix64 draw; 0 keeps none
@@ -124,12 +127,12 @@ struct Config {
   uint32_t* schunk_first;  // [B+1] first pair chunk of frame b
   uint4* schunk;           // [schunk_max] pair chunk k: (first pair, end, frame, first pair of the frame)
   uint2* schunk_frame;     // [schunk_max] pair chunk k: its frame's chunks [x, y)
-  uint32_t* cnt;           // [schunk_max][kSortBins] digit counts of chunk k in a pass
-  // calls whose radix passes have no count launch: [passes][B][fold_rows]
-  // count rows (chunk j of frame b in a pass), cleared by the point filter,
-  // counted with atomics by the launch that writes the pass's pairs (it lies
-  // over hpos and hplace, which are written after the sort)
-  uint32_t* fold_cnt;
+  // digit counts: of chunk k in a pass, [schunk_max][kSortBins]; or (fold_rows
+  // not 0) of chunk j of frame b in every pass, [passes][B][fold_rows][kSortBins],
+  // cleared by the point filter and counted with atomics by the launch that
+  // writes the pass's pairs, over hpos and hplace, which are written after the
+  // sort
+  uint32_t* cnt;
   uint4* vtile;            // [vtile_max] voxel tile t: (first pair, end, frame, first pair of the frame)
   uint32_t* vt_first;      // [B+1] first voxel tile of frame b
   uint32_t* hcount;        // [vtile_max] voxels (heads) of tile t
@@ -165,7 +168,6 @@ struct Config {
   // "not staged"
   int32_t lds_pose_cap, lds_roi_cap, lds_bm_cap, lds_cell_cap, lds_roi, lds_bm, lds_cell, lds_dyn_bytes;
   int32_t lds_wmask;       // the filter's own per-cell ROI words (several words per cell), word offset; -1: none
-  int32_t frame_chunks;    // pair chunks of one frame at most
   int32_t schunk_max;      // bound on pair chunks: min(N / (kSortTile / 2) + B, frame_chunks * B) + 1
   int32_t vtile_max;       // bound on voxel tiles: N / kVoxTile + B + 1
   int32_t mean_grid;

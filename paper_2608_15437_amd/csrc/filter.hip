@@ -818,8 +818,11 @@ __device__ __forceinline__ void fuse_staging(const Config& c, FilterLds& L, Fuse
 
 // Workgroup w: its waves over filter chunks kWaves*w .. kWaves*w + 3.  Per
 // chunk it leaves the bitmap of its kept points, their number, its first
-// point and its frame.  BG: the out-of-ROI keep rate is nonzero.
-template <bool VEC, bool BG, int FS>
+// point and its frame.  BG: the out-of-ROI keep rate is nonzero.  FOLD: it
+// clears the radix passes' count rows too (an instance of its own: a test of
+// fold_rows in every call, a scalar load that each workgroup waits for, took
+// 0.5 us of 16.6 for five frames of 1.3 million points)
+template <bool VEC, bool BG, int FS, bool FOLD>
 __global__ __launch_bounds__(kBlock, 5) void filter_kernel(Config c) {
   __shared__ FilterLds L;
   __shared__ WaveLds Qs[kWaves];
@@ -908,9 +911,9 @@ __global__ __launch_bounds__(kBlock, 5) void filter_kernel(Config c) {
   }
   __syncthreads();
 
-  if (c.fold_rows) {  // uniform: the radix passes' count rows cleared, 16 bytes per thread and step
+  if constexpr (FOLD) {  // the radix passes' count rows cleared, 16 bytes per thread and step
     static_assert(kSortBins % 4 == 0, "16-byte stores");
-    uint4* z = reinterpret_cast<uint4*>(c.fold_cnt);
+    uint4* z = reinterpret_cast<uint4*>(c.cnt);
     const uint32_t n4 = (uint32_t)c.passes * (uint32_t)c.B * (uint32_t)c.fold_rows * (kSortBins / 4);
     for (uint32_t i = blockIdx.x * kBlock + tid; i < n4; i += gridDim.x * kBlock) z[i] = make_uint4(0u, 0u, 0u, 0u);
   }
@@ -929,41 +932,44 @@ __global__ __launch_bounds__(kBlock, 5) void filter_kernel(Config c) {
 
 }  // namespace
 
-hipError_t launch_filter(const Config& c, hipStream_t st) {
-  // one instance per load form and per rate (none, or a nonzero one)
+// one instance per load form and per rate (none, or a nonzero one)
+template <int FS, bool FOLD>
+static void launch_filter_as(const Config& c, hipStream_t st) {
   const dim3 grid(c.filter_grid), block(kBlock);
   const size_t dyn = (size_t)c.lds_dyn_bytes;
+  if (c.vec && c.bg_thr == 0u)
+    hipLaunchKernelGGL((filter_kernel<true, false, FS, FOLD>), grid, block, dyn, st, c);
+  else if (c.vec)
+    hipLaunchKernelGGL((filter_kernel<true, true, FS, FOLD>), grid, block, dyn, st, c);
+  else if (c.bg_thr == 0u)
+    hipLaunchKernelGGL((filter_kernel<false, false, FS, FOLD>), grid, block, dyn, st, c);
+  else
+    hipLaunchKernelGGL((filter_kernel<false, true, FS, FOLD>), grid, block, dyn, st, c);
+}
+
+template <bool FOLD>
+static void launch_filter_fold(const Config& c, hipStream_t st) {
   // FS: 0 the staging kernel's tables, 1 the filter's own (one ROI word
   // per cell), 2 the filter's own with the cells' ROI words in LDS
-  const int fs = c.fuse_stage ? (c.lds_wmask >= 0 ? 2 : 1) : 0;
-  if (fs == 1) {
-    if (c.vec && c.bg_thr == 0u)
-      hipLaunchKernelGGL((filter_kernel<true, false, 1>), grid, block, dyn, st, c);
-    else if (c.vec)
-      hipLaunchKernelGGL((filter_kernel<true, true, 1>), grid, block, dyn, st, c);
-    else if (c.bg_thr == 0u)
-      hipLaunchKernelGGL((filter_kernel<false, false, 1>), grid, block, dyn, st, c);
-    else
-      hipLaunchKernelGGL((filter_kernel<false, true, 1>), grid, block, dyn, st, c);
-  } else if (fs == 2) {
-    if (c.vec && c.bg_thr == 0u)
-      hipLaunchKernelGGL((filter_kernel<true, false, 2>), grid, block, dyn, st, c);
-    else if (c.vec)
-      hipLaunchKernelGGL((filter_kernel<true, true, 2>), grid, block, dyn, st, c);
-    else if (c.bg_thr == 0u)
-      hipLaunchKernelGGL((filter_kernel<false, false, 2>), grid, block, dyn, st, c);
-    else
-      hipLaunchKernelGGL((filter_kernel<false, true, 2>), grid, block, dyn, st, c);
-  } else if (c.vec && c.bg_thr == 0u) {
-    hipLaunchKernelGGL((filter_kernel<true, false, 0>), grid, block, dyn, st, c);
-  } else if (c.vec) {
-    hipLaunchKernelGGL((filter_kernel<true, true, 0>), grid, block, dyn, st, c);
-  } else if (c.bg_thr == 0u) {
-    hipLaunchKernelGGL((filter_kernel<false, false, 0>), grid, block, dyn, st, c);
-  } else {
-    hipLaunchKernelGGL((filter_kernel<false, true, 0>), grid, block, dyn, st, c);
-  }
+  if (c.fuse_stage && c.lds_wmask < 0)
+    launch_filter_as<1, FOLD>(c, st);
+  else if (c.fuse_stage)
+    launch_filter_as<2, FOLD>(c, st);
+  else
+    launch_filter_as<0, FOLD>(c, st);
+}
+
+#ifndef MMBEV_SMALL_CALLS
+hipError_t launch_filter(const Config& c, hipStream_t st) {
+  if (c.fold_rows) return launch_filter_small(c, st);
+  launch_filter_fold<false>(c, st);
   return hipGetLastError();
 }
+#else
+hipError_t launch_filter_small(const Config& c, hipStream_t st) {
+  launch_filter_fold<true>(c, st);
+  return hipGetLastError();
+}
+#endif
 
 }  // namespace mmbev

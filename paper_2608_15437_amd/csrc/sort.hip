@@ -85,9 +85,9 @@ __device__ __forceinline__ void fold_count(uint32_t* rows, uint32_t j, uint32_t 
     __hip_atomic_fetch_add(&rows[j * kSortBins + dig], (uint32_t)__popcll(same), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The fold_cnt rows of frame b in a pass.
+// The count rows of frame b in a pass (calls whose passes have no count launch).
 __device__ __forceinline__ uint32_t* fold_rows_of(const Config& c, int pass, uint32_t b) {
-  return c.fold_cnt + (size_t)((uint32_t)pass * (uint32_t)c.B + b) * (uint32_t)c.fold_rows * kSortBins;
+  return c.cnt + (size_t)((uint32_t)pass * (uint32_t)c.B + b) * (uint32_t)c.fold_rows * kSortBins;
 }
 
 constexpr int kSegBlock = 1024;  // threads of the segments kernel
@@ -101,9 +101,9 @@ constexpr int kSegPreLds = 16384;  // kept-pair prefixes of up to this many filt
 // end; otherwise in the workspace directly (the s_ arrays unused).  (One
 // address space per instance: a pointer that may be either compiles to
 // generic instructions, whose waits cover both kinds of access.)  s_tmp
-// holds 2 * BLOCK / 64 words.
+// holds 2 * BLOCK / 64 words.  mc: pair chunks of one frame at most.
 template <bool kLds, int BLOCK>
-__device__ __forceinline__ void segments_body(const Config& c, uint32_t* s_tmp, uint32_t* s_fstart, uint32_t* s_sfirst,
+__device__ __forceinline__ void segments_body(const Config& c, const uint32_t mc, uint32_t* s_tmp, uint32_t* s_fstart, uint32_t* s_sfirst,
                                               uint32_t* s_tfirst, uint32_t* s_pre, unsigned long long* s_most) {
   WsHeader* h = c.hdr;
   const int tid = threadIdx.x;
@@ -188,7 +188,7 @@ __device__ __forceinline__ void segments_body(const Config& c, uint32_t* s_tmp, 
   // the frames' counts scanned into their first indices, then every chunk
   // and tile written by its own thread (its frame found by a search over
   // the first indices: the last frame whose first index is at most its own)
-  const uint32_t mt = chunk_min_tiles(K, c.B), mc = (uint32_t)c.frame_chunks;
+  const uint32_t mt = chunk_min_tiles(K, c.B);
   const bool half = half_tile_chunks(K, c.B);
   const int per = (c.B + BLOCK - 1) / BLOCK;
   const int b0 = tid * per;
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(kSegBlock) void segments_kernel(Config c) {
   __shared__ uint32_t s_tfirst[kLds ? kSegLdsFrames + 1 : 1];  // first voxel tile of every frame
   __shared__ uint32_t s_pre[kLds ? kSegPreLds + 1 : 1];        // kept pairs of the filter chunks before k
   __shared__ unsigned long long s_most;  // (pairs, ~frame) of the frame with the most pairs
-  segments_body<kLds, kSegBlock>(c, s_tmp, s_fstart, s_sfirst, s_tfirst, s_pre, &s_most);
+  segments_body<kLds, kSegBlock>(c, kMaxFrameChunks, s_tmp, s_fstart, s_sfirst, s_tfirst, s_pre, &s_most);
 }
 
 // Sums of four values over the workgroup (s_tmp: 4 * WAVES words).
@@ -334,11 +334,11 @@ __global__ __launch_bounds__(kCompactBlock) void compact_kernel(Config c, uint32
   static_assert(kChunkWords <= kCompactBlock, "one bitmap word per thread");
   extern __shared__ float s_pose[];  // [S][12]
   __shared__ uint16_t s_list[kMaxChunkPoints];  // kept point offsets in the chunk, ascending
-  __shared__ uint32_t s_tmp[4 * kCompactWaves];
+  __shared__ uint32_t s_tmp[(kSmall ? 4 : 3) * kCompactWaves];
   __shared__ unsigned long long s_most;
   const int tid = threadIdx.x;
   if (kSmall && blockIdx.x == gridDim.x - 1) {  // uniform: the segments kernel's work
-    segments_body<false, kCompactBlock>(c, s_tmp, nullptr, nullptr, nullptr, nullptr, &s_most);
+    segments_body<false, kCompactBlock>(c, (uint32_t)c.frame_chunks, s_tmp, nullptr, nullptr, nullptr, nullptr, &s_most);
     return;
   }
   const uint32_t k = blockIdx.x;
@@ -531,8 +531,6 @@ __global__ __launch_bounds__(kBlock) void count_kernel(Config c, int pass, const
       count_chunk<1>(c, s_hist, k, ch.x, ch.y, kin, shift, mask, nbins);
   }
 }
-
-constexpr int kSmallRows = 32;  // count rows in flight of a scatter workgroup of a small call
 
 struct ScatterLds {
   uint32_t pos[kSortBins];             // per digit: output position of the tile's pair i of that digit, less i
@@ -796,6 +794,7 @@ __global__ __launch_bounds__(kBlock, PER_CU) void scatter_kernel(Config c, int p
 
 }  // namespace
 
+#ifndef MMBEV_SMALL_CALLS
 hipError_t launch_segments(const Config& c, hipStream_t st) {
   if (c.B <= kSegLdsFrames)
     hipLaunchKernelGGL(segments_kernel<true>, dim3(1), dim3(kSegBlock), 0, st, c);
@@ -805,28 +804,19 @@ hipError_t launch_segments(const Config& c, hipStream_t st) {
 }
 
 hipError_t launch_compact(const Config& c, uint32_t* kout, hipStream_t st) {
+  if (c.small_call) return launch_compact_small(c, kout, st);
   const size_t lds = (size_t)c.S * 12 * sizeof(float);
-  const dim3 grid(c.fchunk_max + (c.small_call ? 1 : 0));  // small calls: one more workgroup for the segments' work
-  if (c.fchunk_points <= kCompactSmallChunk) {
-    if (c.small_call)
-      hipLaunchKernelGGL((compact_kernel<128, true>), grid, dim3(128), lds, st, c, kout);
-    else
-      hipLaunchKernelGGL((compact_kernel<128, false>), grid, dim3(128), lds, st, c, kout);
-  } else if (c.small_call) {
-    hipLaunchKernelGGL((compact_kernel<kBlock, true>), grid, dim3(kBlock), lds, st, c, kout);
-  } else {
+  const dim3 grid(c.fchunk_max);
+  if (c.fchunk_points <= kCompactSmallChunk)
+    hipLaunchKernelGGL((compact_kernel<128, false>), grid, dim3(128), lds, st, c, kout);
+  else
     hipLaunchKernelGGL((compact_kernel<kBlock, false>), grid, dim3(kBlock), lds, st, c, kout);
-  }
   return hipGetLastError();
 }
 
 hipError_t launch_radix_pass(const Config& c, int pass, const uint32_t* kin, const uint32_t* vin, uint32_t* kout,
                              uint32_t* vout, hipStream_t st) {
-  if (c.fold_rows) {  // counted by the launch before
-    hipLaunchKernelGGL((scatter_kernel<kSmallRows, 2, true>), dim3((uint32_t)c.schunk_max), dim3(kBlock), 0, st, c, pass, kin,
-                       vin, kout, vout);
-    return hipGetLastError();
-  }
+  if (c.fold_rows) return launch_scatter_small(c, pass, kin, vin, kout, vout, st);
   // grids of resident size (idle workgroups still cost dispatch time)
   const uint32_t cgrid = min((uint32_t)c.schunk_max, (uint32_t)kCountGrid);
   hipLaunchKernelGGL(count_kernel, dim3(cgrid), dim3(kBlock), 0, st, c, pass, kin);
@@ -837,5 +827,24 @@ hipError_t launch_radix_pass(const Config& c, int pass, const uint32_t* kin, con
                      vout);
   return hipGetLastError();
 }
+#else
+hipError_t launch_compact_small(const Config& c, uint32_t* kout, hipStream_t st) {
+  const size_t lds = (size_t)c.S * 12 * sizeof(float);
+  const dim3 grid(c.fchunk_max + 1);  // one more workgroup for the segments' work
+  if (c.fchunk_points <= kCompactSmallChunk)
+    hipLaunchKernelGGL((compact_kernel<128, true>), grid, dim3(128), lds, st, c, kout);
+  else
+    hipLaunchKernelGGL((compact_kernel<kBlock, true>), grid, dim3(kBlock), lds, st, c, kout);
+  return hipGetLastError();
+}
+
+// a pass whose digits the launch before has counted
+hipError_t launch_scatter_small(const Config& c, int pass, const uint32_t* kin, const uint32_t* vin, uint32_t* kout,
+                                uint32_t* vout, hipStream_t st) {
+  hipLaunchKernelGGL((scatter_kernel<32, 2, true>), dim3((uint32_t)c.schunk_max), dim3(kBlock), 0, st, c, pass, kin, vin,
+                     kout, vout);
+  return hipGetLastError();
+}
+#endif
 
 }  // namespace mmbev

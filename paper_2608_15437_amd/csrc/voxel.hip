@@ -538,21 +538,25 @@ __global__ __launch_bounds__(kBlock, PER_CU) void mean_kernel(Config c, const ui
     double sum[8];
 #pragma unroll
     for (int f = 0; f < 8; ++f) sum[f] = 0.0;
-    auto places = [&](uint32_t m0, uint32_t* q) {
+    uint32_t qn[BATCH];  // small calls: the next batch's places, loaded with this batch's records
+    auto places = [&](uint32_t m0) {
 #pragma unroll
       for (int u = 0; u < BATCH; ++u)
-        q[u] = min(m0 + u == 0 ? q0 : vals[min(s0 + (BATCH > 2 ? min(m0 + u, cnt - 1u) : m0 + u), K - 1u)], K - 1u);
+        qn[u] = min(m0 + u == 0 ? q0 : vals[min(s0 + min(m0 + u, cnt - 1u), K - 1u)], K - 1u);
     };
-    uint32_t qn[BATCH];  // small calls: the next batch's places, loaded with this batch's records
-    if (BATCH > 2 && cnt > 0u) places(0u, qn);
+    if constexpr (BATCH > 2) {
+      if (cnt > 0u) places(0u);
+    }
     for (uint32_t m0 = 0; m0 < cnt; m0 += BATCH) {
       uint32_t q[BATCH];
-      if (BATCH > 2) {
+      if constexpr (BATCH > 2) {
 #pragma unroll
         for (int u = 0; u < BATCH; ++u) q[u] = qn[u];
-        places(m0 + BATCH, qn);  // past the last point: its place again
+        places(m0 + BATCH);  // past the last point: its place again
       } else {
-        places(m0, q);
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u)
+          q[u] = min(m0 + u == 0 ? q0 : vals[min(s0 + m0 + u, K - 1u)], K - 1u);
       }
       uint32_t w[BATCH][RW];
 #pragma unroll
@@ -629,6 +633,23 @@ __global__ __launch_bounds__(kBlock, PER_CU) void mean_kernel(Config c, const ui
 
 }  // namespace
 
+// one instance per record width (point index, x', y', z', raw features 3..)
+template <int BATCH, int PER_CU>
+static hipError_t launch_mean_as(const Config& c, const uint32_t* keys, const uint32_t* vals, hipStream_t st) {
+  const dim3 grid(c.mean_grid), block(kBlock);
+  const size_t lds = (size_t)kMeanTile * (4 + c.C + c.M) * 4;
+  if (c.rec_words == 4)
+    hipLaunchKernelGGL((mean_kernel<4, BATCH, PER_CU>), grid, block, lds, st, c, keys, vals);
+  else if (c.rec_words == 6)
+    hipLaunchKernelGGL((mean_kernel<6, BATCH, PER_CU>), grid, block, lds, st, c, keys, vals);
+  else if (c.rec_words == 8)
+    hipLaunchKernelGGL((mean_kernel<8, BATCH, PER_CU>), grid, block, lds, st, c, keys, vals);
+  else
+    hipLaunchKernelGGL((mean_kernel<10, BATCH, PER_CU>), grid, block, lds, st, c, keys, vals);
+  return hipGetLastError();
+}
+
+#ifndef MMBEV_SMALL_CALLS
 hipError_t launch_heads(const Config& c, const uint32_t* keys, const uint32_t* vals, hipStream_t st) {
   // a grid of resident size (six per CU by registers) walks the tiles
   hipLaunchKernelGGL(heads_kernel, dim3(std::min(c.vtile_max, 6 * kCus)), dim3(kBlock), 0, st, c, keys, vals);
@@ -641,24 +662,12 @@ hipError_t launch_fincap(const Config& c, hipStream_t st) {
 }
 
 hipError_t launch_mean(const Config& c, const uint32_t* keys, const uint32_t* vals, hipStream_t st) {
-  const size_t lds = (size_t)kMeanTile * (4 + c.C + c.M) * 4;
-  // one instance per record width (point index, x', y', z', raw features 3..) and call size
-#define MMBEV_MEAN(RW)                                                                                       \
-  if (c.small_call)                                                                                          \
-    hipLaunchKernelGGL((mean_kernel<RW, 4, 4>), dim3(c.mean_grid), dim3(kBlock), lds, st, c, keys, vals);    \
-  else                                                                                                       \
-    hipLaunchKernelGGL((mean_kernel<RW, 2, 6>), dim3(c.mean_grid), dim3(kBlock), lds, st, c, keys, vals)
-  if (c.rec_words == 4) {
-    MMBEV_MEAN(4);
-  } else if (c.rec_words == 6) {
-    MMBEV_MEAN(6);
-  } else if (c.rec_words == 8) {
-    MMBEV_MEAN(8);
-  } else {
-    MMBEV_MEAN(10);
-  }
-#undef MMBEV_MEAN
-  return hipGetLastError();
+  return c.small_call ? launch_mean_small(c, keys, vals, st) : launch_mean_as<2, 6>(c, keys, vals, st);
 }
+#else
+hipError_t launch_mean_small(const Config& c, const uint32_t* keys, const uint32_t* vals, hipStream_t st) {
+  return launch_mean_as<4, 4>(c, keys, vals, st);
+}
+#endif
 
 }  // namespace mmbev
