@@ -18,7 +18,6 @@ hipError_t launch_fincap(const Config& c, hipStream_t st);
 hipError_t launch_mean(const Config& c, const uint32_t* keys, const uint32_t* vals, hipStream_t st);
 // small calls' own instances of the same (small_calls.hip)
 hipError_t launch_filter_small(const Config& c, hipStream_t st);
-hipError_t launch_compact_small(const Config& c, uint32_t* kout, hipStream_t st);
 hipError_t launch_scatter_small(const Config& c, int pass, const uint32_t* kin, const uint32_t* vin, uint32_t* kout,
                                 uint32_t* vout, hipStream_t st);
 hipError_t launch_mean_small(const Config& c, const uint32_t* keys, const uint32_t* vals, hipStream_t st);

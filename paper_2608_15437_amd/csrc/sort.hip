@@ -756,9 +756,9 @@ __device__ __forceinline__ void scatter_chunk(const Config& c, ScatterLds& L, in
 // whose workgroups must fit kScatterPerCu to a compute unit and hide each
 // other's trips; 32 for small ones (at most kSmallChunks filter chunks), whose
 // few chunks leave the chip idle, where the registers of the rows cost nothing.
-template <int ROWS, int PER_CU, bool FOLD>
-__global__ __launch_bounds__(kBlock, PER_CU) void scatter_kernel(Config c, int pass, const uint32_t* kin, const uint32_t* vin,
-                                                         uint32_t* kout, uint32_t* vout) {
+template <int ROWS, bool FOLD>
+__device__ __forceinline__ void scatter_body(const Config& c, int pass, const uint32_t* kin, const uint32_t* vin, uint32_t* kout,
+                                             uint32_t* vout) {
   __shared__ ScatterLds L;
   static_assert(sizeof(ScatterLds) <= 160 * 1024 / kScatterPerCu, "workgroups per CU");
   static_assert(kSortBins == 2 * kBlock, "two digits per thread");
@@ -792,6 +792,22 @@ __global__ __launch_bounds__(kBlock, PER_CU) void scatter_kernel(Config c, int p
   }
 }
 
+// (Plain kernels, emitted in this order: with the count and scatter kernels,
+// which take turns, next to each other five frames of 1.3 million points took
+// 85.4 us a call; with the segments and compaction kernels between them,
+// 85.8.)
+#ifndef MMBEV_SMALL_CALLS
+__global__ __launch_bounds__(kBlock, kScatterPerCu) void scatter_kernel(Config c, int pass, const uint32_t* kin, const uint32_t* vin,
+                                                                        uint32_t* kout, uint32_t* vout) {
+  scatter_body<8, false>(c, pass, kin, vin, kout, vout);
+}
+#else
+__global__ __launch_bounds__(kBlock, 2) void scatter_small_kernel(Config c, int pass, const uint32_t* kin, const uint32_t* vin,
+                                                                  uint32_t* kout, uint32_t* vout) {
+  scatter_body<32, true>(c, pass, kin, vin, kout, vout);
+}
+#endif
+
 }  // namespace
 
 #ifndef MMBEV_SMALL_CALLS
@@ -804,13 +820,18 @@ hipError_t launch_segments(const Config& c, hipStream_t st) {
 }
 
 hipError_t launch_compact(const Config& c, uint32_t* kout, hipStream_t st) {
-  if (c.small_call) return launch_compact_small(c, kout, st);
   const size_t lds = (size_t)c.S * 12 * sizeof(float);
-  const dim3 grid(c.fchunk_max);
-  if (c.fchunk_points <= kCompactSmallChunk)
-    hipLaunchKernelGGL((compact_kernel<128, false>), grid, dim3(128), lds, st, c, kout);
-  else
+  const dim3 grid(c.fchunk_max + (c.small_call ? 1 : 0));  // small calls: one more workgroup for the segments' work
+  if (c.fchunk_points <= kCompactSmallChunk) {
+    if (c.small_call)
+      hipLaunchKernelGGL((compact_kernel<128, true>), grid, dim3(128), lds, st, c, kout);
+    else
+      hipLaunchKernelGGL((compact_kernel<128, false>), grid, dim3(128), lds, st, c, kout);
+  } else if (c.small_call) {
+    hipLaunchKernelGGL((compact_kernel<kBlock, true>), grid, dim3(kBlock), lds, st, c, kout);
+  } else {
     hipLaunchKernelGGL((compact_kernel<kBlock, false>), grid, dim3(kBlock), lds, st, c, kout);
+  }
   return hipGetLastError();
 }
 
@@ -823,26 +844,14 @@ hipError_t launch_radix_pass(const Config& c, int pass, const uint32_t* kin, con
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const uint32_t sgrid = min((c.schunk_max + 7u) / 8u * 8u, (uint32_t)(kScatterPerCu * kCus));  // whole rounds of the XCDs
-  hipLaunchKernelGGL((scatter_kernel<8, kScatterPerCu, false>), dim3(sgrid), dim3(kBlock), 0, st, c, pass, kin, vin, kout,
-                     vout);
+  hipLaunchKernelGGL(scatter_kernel, dim3(sgrid), dim3(kBlock), 0, st, c, pass, kin, vin, kout, vout);
   return hipGetLastError();
 }
 #else
-hipError_t launch_compact_small(const Config& c, uint32_t* kout, hipStream_t st) {
-  const size_t lds = (size_t)c.S * 12 * sizeof(float);
-  const dim3 grid(c.fchunk_max + 1);  // one more workgroup for the segments' work
-  if (c.fchunk_points <= kCompactSmallChunk)
-    hipLaunchKernelGGL((compact_kernel<128, true>), grid, dim3(128), lds, st, c, kout);
-  else
-    hipLaunchKernelGGL((compact_kernel<kBlock, true>), grid, dim3(kBlock), lds, st, c, kout);
-  return hipGetLastError();
-}
-
 // a pass whose digits the launch before has counted
 hipError_t launch_scatter_small(const Config& c, int pass, const uint32_t* kin, const uint32_t* vin, uint32_t* kout,
                                 uint32_t* vout, hipStream_t st) {
-  hipLaunchKernelGGL((scatter_kernel<32, 2, true>), dim3((uint32_t)c.schunk_max), dim3(kBlock), 0, st, c, pass, kin, vin,
-                     kout, vout);
+  hipLaunchKernelGGL(scatter_small_kernel, dim3((uint32_t)c.schunk_max), dim3(kBlock), 0, st, c, pass, kin, vin, kout, vout);
   return hipGetLastError();
 }
 #endif
