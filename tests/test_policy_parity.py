@@ -62,21 +62,46 @@ def test_ties_and_exact_boundaries(mb):
     _same(*_both(mb, d, np.array([0, 6], np.int32), e, dict(POL)))
 
 
-@pytest.mark.parametrize("count,copies,theta", [(1, 1, 60.0), (64, 1, 15.0), (126, 2, 89.5), (128, 1, 90.0), (129, 1, 0.0),
+def _order_words(d, crit, pol):
+    """Ranking keys of detections whose ego frame did not move, and the 32-bit words that order them up to ties: 30 bits
+    of the TTC or, without one, of the distance."""
+    x, y = d["x"] + d["vx"] * pol["dt"], d["y"] + d["vy"] * pol["dt"]
+    dist, ttc, opt = np.sqrt(x * x + y * y), crit["ttc"].copy(), (crit["flags"] & 4) == 0
+    bits = np.where(np.isinf(ttc), (1 << 30) | (dist.view(np.int64) >> 33), ttc.view(np.int64) >> 33)
+    return list(zip(opt, ttc, dist)), bits | opt.astype(np.int64) << 31
+
+
+@pytest.mark.parametrize("count,copies,theta", [(1, 1, 60.0), (64, 2, 15.0), (126, 2, 89.5), (128, 2, 90.0), (129, 3, 0.0),
                                                (128, 3, 89.0)])
 def test_ranking_and_cone_edges(mb, count, copies, theta):
-    """Frames up to and past the largest that is ranked by counting, equal and nearly equal ranking keys (repeated
-    detections, positions one unit in the last place apart), detections on the cone's edge to the last bits, and cones
-    on both sides of the steepest that is decided by the tangent."""
+    """Frames up to and past the largest that is ranked by counting, with equal ranking keys (detections repeated in
+    their frame) and keys that differ in their last bits only, the larger one first (one of a pair a little farther
+    away), with and without a TTC; detections on the cone's edge to the last bits, and cones on both sides of the
+    steepest that is decided by the tangent."""
     d, off, e = synth.detections(70 + count, 3, count=[count, 0, count])
-    n = len(d)
-    d[:n - n // copies] = d[n // copies:][:n - n // copies] if copies > 1 else d[:0]
-    d["x"][::5] = np.nextafter(d["x"][::5], np.inf)
-    d["vx"][1::4] = d["vy"][1::4] = 0.0
     e["dyaw"], e["dx"], e["dy"] = 0.0, 0.0, 0.0
+    d["vx"][1::4] = d["vy"][1::4] = 0.0
     d["x"][1::4] = np.abs(d["x"][1::4])
     d["y"][1::4] = d["x"][1::4] * np.tan(np.radians(theta)) * (1.0 + np.arange(len(d[1::4])) % 5 * 2.0 ** -52)
-    _same(*_both(mb, d, off, e, dict(POL, theta_max_deg=theta, theta_min_deg=theta)))
+    part = count // copies
+    for lo in (0, count):
+        for k in range(1, copies):
+            d[lo + k * part:lo + (k + 1) * part] = d[lo:lo + part]
+        for k in range(lo, lo + part, 3):  # the first of the copies
+            for c in ("x", "y"):
+                d[c][k] += np.sign(d[c][k]) * 4 * np.spacing(abs(d[c][k]))
+    pol = dict(POL, theta_max_deg=theta, theta_min_deg=theta)
+    got, exp = _both(mb, d, off, e, pol)
+    _same(got, exp)
+    if copies > 1:  # equal words of different keys, the larger key first, with a TTC and without; equal keys
+        seen = set()
+        for lo in (0, count):
+            key, word = _order_words(d[lo:lo + count], got["crit"][lo:lo + count], pol)
+            for a in range(count):
+                for b in range(a + 1, count):
+                    if word[a] == word[b]:
+                        seen.add((bool(np.isinf(key[a][1])), "larger" if key[a] > key[b] else "less" if key[a] < key[b] else "same"))
+        assert {(True, "larger"), (True, "same"), (False, "larger"), (False, "same")} <= seen, seen
 
 
 def test_rejects_bad_arguments(mb):
