@@ -136,9 +136,16 @@ mmbev_status_t make_plan(const mmbev_grid_t* g, int64_t N, int32_t max_rois, int
     p->filter_grid = std::max<int64_t>(1, (p->fchunk_max + kWaves - 1) / kWaves);
   }
   // small calls of a few frames count each radix pass's digits where its
-  // pairs are written: rows for every chunk a frame can have, as long as they
-  // fit the space of hpos and hplace (from about 2,000 points on).  With room
-  // for twice the rows a frame may have twice the chunks: a frame of 250,000
+  // pairs are written, as long as the passes' count rows, for every chunk a
+  // frame can have, fit the space of hpos and hplace (2 N words).  The rows
+  // grow with N / 1,024 up to the chunk limit, so for one frame of three
+  // passes they fit from 2,304 points on (and at some sizes from 768 on); at
+  // passes * frames >= 4 only once the limit holds, from 16,384 points per
+  // pass and frame on: one frame of four passes from 65,536, two frames of
+  // three from 98,304, eight from 393,216 (eight of four passes: past the
+  // limit of filter chunks).  Smaller calls of several frames keep their
+  // count launches.  With room for twice the rows (32,768 points
+  // per pass and frame) a frame may have twice the chunks: a frame of 250,000
   // pairs has one tile to a workgroup then instead of two, and twice as many
   // compute units at work (its three scatter launches 53.7 -> 51.9 us; its
   // workgroups sum twice the rows).

@@ -226,7 +226,7 @@ __device__ __forceinline__ int32_t cc_run_start(const CcConfig& c, int32_t x, in
 // u's first join, to the run of its occupied neighbour n (n < u, in column
 // col): u is nearly always still its own root, and one compare-and-swap links
 // it, without walking the two trees first.  (The kernel: one frame of 21,421
-// rows 36 -> 27 us, 128 frames 66 -> 58 us; what is left are the walks of the
+// rows 34 -> 27 us, 128 frames 63 -> 58 us; what is left are the walks of the
 // second joins, a device-wide round trip per step.)
 __device__ __forceinline__ void cc_link(const CcConfig& c, int32_t u, int32_t n, int32_t col) {
   const int32_t t = cc_run_start(c, n, col);
@@ -329,6 +329,7 @@ __global__ __launch_bounds__(kBlock) void cc_blocksum_kernel(CcConfig c) {
 __global__ __launch_bounds__(kBlock) void cc_init_kernel(CcConfig c) {
   __shared__ uint32_t s_tmp[kWaves];
   __shared__ uint32_t s_blk[kCcWords];
+  static_assert(kCcMaxCells / 32 / kCcWords <= kCcWords, "a place per scan block");
   const int64_t V = cc_rows(c);
   const int64_t stride = (int64_t)gridDim.x * kBlock;
   const int64_t g0 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -402,9 +403,10 @@ struct CcTable {
 // contiguous part of the rows and sums it per cluster in LDS first: atomics
 // on one cluster's line serialise, and a cluster's rows come once per layer,
 // many short runs each.  A frame's clusters have consecutive indices, so the
-// table's first place is free or the cluster's own unless the part holds
-// more than kCcTable clusters; a run that finds no place in a few steps goes
-// to memory.  (One frame of 21,421 rows with one large cluster 48 -> 9 us;
+// table's first place is free or the cluster's own unless the part's cluster
+// indices span more than kCcTable (a sparse upper layer, or the end of one
+// layer and the start of the next); a run that finds no place in a few steps
+// goes to memory.  (One frame of 21,421 rows with one large cluster 48 -> 9 us;
 // 128 frames, 903,061 rows, 106 -> 29 us.)
 __global__ __launch_bounds__(kCcAccumBlock) void cc_accum_kernel(CcConfig c) {
   __shared__ CcTable T;

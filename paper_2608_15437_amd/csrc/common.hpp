@@ -90,8 +90,10 @@ struct Config {
   int32_t cell_pad;        // voxels added around each ROI's cell rectangle
   uint32_t Dx, Dy, Dz;
   int32_t cell_shift, ncx, ncy, ncells;
-  // (the order and widths keep these where the kernels load them in one go:
-  // three words in a row that a kernel reads become a load of four)
+  // (fold_rows lies apart from passes and dbits: three words in a row that a
+  // kernel reads become a load of four, and the scatter's next scalar load
+  // waited for its unused fourth, one frame 57.3 -> 58.0 us a call.  vec and
+  // fuse_stage, which only the host reads, are narrow to make room.)
   int32_t frame_chunks;  // pair chunks of one frame at most
   // keys: (iz*Dy + iy)*Dx + ix, sorted within each frame in `passes`
   // least-significant-digit passes of dbits bits

@@ -821,7 +821,7 @@ __device__ __forceinline__ void fuse_staging(const Config& c, FilterLds& L, Fuse
 // point and its frame.  BG: the out-of-ROI keep rate is nonzero.  FOLD: it
 // clears the radix passes' count rows too (an instance of its own: a test of
 // fold_rows in every call, a scalar load that each workgroup waits for, took
-// 0.5 us of 16.6 for five frames of 1.3 million points)
+// 0.6 us on 16.6 for five frames of 1.3 million points)
 template <bool VEC, bool BG, int FS, bool FOLD>
 __global__ __launch_bounds__(kBlock, 5) void filter_kernel(Config c) {
   __shared__ FilterLds L;

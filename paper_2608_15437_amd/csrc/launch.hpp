@@ -49,7 +49,7 @@ struct CcHeader {
 constexpr uint32_t kCcRowGrid = 8192;     // workgroups of the per-row launches (they loop)
 constexpr uint32_t kCcInitGrid = 1024;    // ... of the launch whose workgroups each scan the block sums (four per CU)
 constexpr uint32_t kCcAccumGrid = 512;    // ... of the accumulation (1,024 threads: two per CU)
-constexpr int64_t kCcMaxCells = (int64_t)1 << 29;  // cells over all frames (single-workgroup block scan)
+constexpr int64_t kCcMaxCells = (int64_t)1 << 29;  // cells over all frames (each workgroup of the init kernel holds the scan blocks' sums in LDS)
 
 struct CcConfig {
   const int4* coords;       // [rows]

@@ -422,8 +422,8 @@ __global__ __launch_bounds__(kFinBlock) void fincap_kernel(Config c) {
 // occupancy through their registers, one adds round trips); four for small
 // ones (at most kSmallChunks filter chunks), whose voxels do not fill the
 // chip: a voxel's points take half the dependent round trips (place, record).
-// (One frame, 7,265 voxels: 10.2 -> 9.3 us; with eight 9.4, but 12.3 -> 13.7
-// for 108,862 voxels, where four take 12.3 too.)
+// (One frame, 7,265 voxels: 10.1 -> 9.6 us, and 108,877 voxels 12.2 either way;
+// with eight, before the next places were loaded ahead, 9.4 and 13.7.)
 template <int RW, int BATCH, int PER_CU>
 __global__ __launch_bounds__(kBlock, PER_CU) void mean_kernel(Config c, const uint32_t* keys, const uint32_t* vals) {
   extern __shared__ uint32_t sm[];
